@@ -42,7 +42,7 @@ constexpr size_t kAlign = 256;
 struct Plan {
     size_t total = 0;
     size_t tabD, tabF, tabW, geoD, geoW, pcode, bpos, xyz, wJ, J, Gm, invw, invMb, bmap, bown, goff, gmem, ftag,
-        wallu, f[4], rtb, rhoc, Fn, io, red, flag, posmap, hidx, nbr = 0, cl_params = 0, cl_X = 0, cl_dtau = 0;
+        wallu, f[4], rtb, rhoc, Fn, io, red, flag, posmap, hidx, nbr = 0, tabL, aff = 0, cl_params = 0, cl_X = 0, cl_dtau = 0;
     int nred = 0;
     bool closure = false;
 };
@@ -112,6 +112,8 @@ Plan make_plan(const sel_mesh *m, const sel_params *p)
     L.tabD = carve(c, ts * n1 * n1);
     L.tabF = carve(c, ts * n1 * n1);
     L.tabW = carve(c, ts * n1);
+    L.tabL = carve(c, ts * sel::kLineTab);
+    if (!m->aff.empty()) L.aff = carve(c, ts * m->aff.size());
     L.geoD = carve(c, 8 * n1 * n1);
     L.geoW = carve(c, 8 * n1);
     L.pcode = carve(c, 4 * np);
@@ -183,6 +185,14 @@ int upload_tables(sel_sim *s, const sel::Tables &t, const sel_mesh *m, std::vect
     if (put(s->tabW, Wt.data(), sizeof(T) * Wt.size())) return SEL_EDEVICE;
     if (put(s->geoD, D.data(), 8 * D.size())) return SEL_EDEVICE;
     if (put(s->geoW, W.data(), 8 * W.size())) return SEL_EDEVICE;
+    double lt[sel::kLineTab] = {};
+    const int nlt = sel::find_ops(m->dim, m->N, s->Q, s->prec)->line_tables(t, lt);
+    std::vector<T> Lt = conv<T>(lt, nlt);
+    if (put(s->tabL, Lt.data(), sizeof(T) * Lt.size())) return SEL_EDEVICE;
+    if (s->aff) {
+        std::vector<T> Af = conv<T>(m->aff.data(), m->aff.size());
+        if (put(s->aff, Af.data(), sizeof(T) * Af.size())) return SEL_EDEVICE;
+    }
     std::vector<T> wu = conv<T>(m->wall_u.data(), m->wall_u.size());
     if (put(s->wallu, wu.data(), sizeof(T) * wu.size())) return SEL_EDEVICE;
     return SEL_OK;
@@ -302,6 +312,7 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     s->nstate = (int64_t)p->Q * (s->Gi + (m->ngrp + 63) / 64 * 64);
     s->nwall = m->nwall;
     s->p = *p;
+    s->tab = tab;
     s->prec = p->precision;
     s->tsize = (p->precision == SEL_FP32_DEV) ? 4 : 8;
     const double cs2 = 1.0 / 3.0;
@@ -335,6 +346,8 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     s->tabD = b + L.tabD;
     s->tabF = b + L.tabF;
     s->tabW = b + L.tabW;
+    s->tabL = b + L.tabL;
+    if (!m->aff.empty()) s->aff = b + L.aff;
     s->geoD = reinterpret_cast<double *>(b + L.geoD);
     s->geoW = reinterpret_cast<double *>(b + L.geoW);
     s->pcode = reinterpret_cast<int32_t *>(b + L.pcode);

@@ -4,6 +4,7 @@
 #include "kernels_big.h"
 #include "kernels_impl.h"
 #include "kernels_mfma.h"
+#include "kernels_stream.h"
 #include "ops.h"
 
 namespace sel {
@@ -116,9 +117,63 @@ struct Impl {
         return hipEventRecord(b, s->stream) == hipSuccess ? SEL_OK : SEL_EDEVICE;
     }
 
+    // affine elements (3D): one streaming pass (kernels_stream.h) with the operands of A
+    static int launch_stream(sel_sim *s, const StageArgs<T> &A)
+    {
+        using SG = StreamGeo<N, Q, T>;
+        StreamArgs<N, Q, T> S{};
+        S.op = A.op;
+        S.f0in = A.f0in;
+        S.out = A.out;
+        S.rtb = A.rtb;
+        S.rhoc = A.rhoc;
+        S.wallu = A.wallu;
+        S.Fn = nullptr;
+        S.bpos = A.bpos;
+        S.bmap = A.bmap;
+        S.posmap = A.posmap;
+        S.ftag = A.ftag;
+        S.E = A.E;
+        S.QGi = A.QGi;
+        S.plane = A.plane;
+        S.ca = A.ca;
+        S.cb = A.cb;
+        S.cc = A.cc;
+        S.rho0 = A.rho0;
+        S.incr = A.incr;
+        S.tab = static_cast<const T *>(s->tabL);
+        S.aff = static_cast<const T *>(s->aff);
+        for (int i = 0; i <= N; ++i) S.w[i] = T(s->tab.w[i]);
+        int n = 0;
+        for (int a = 1; a < Q; ++a) {
+            const int b = lat_opp<DIM, Q>(a);
+            if (b < a) continue;
+            S.pa[n] = a;
+            S.pb[n] = b;
+            for (int c = 0; c < 3; ++c) S.pe[n][c] = T(lat_e<DIM, Q>(a, c));
+            S.pt[n] = T(lat_t<DIM, Q>(a));
+            S.pf[n] = A.fsc[a];
+            S.body |= A.fsc[a] != T(0);
+            ++n;
+        }
+        hipEvent_t ev = nullptr;
+        if (int rc = tic(s, 1, ev)) return rc;
+        const dim3 grid((unsigned)xcd_grid(A.E)), block(SG::BLOCK);
+        if (s->nwall > 0) {
+            hipLaunchKernelGGL((k_stream<N, Q, T, true>), grid, block, 0, s->stream, S);
+        } else {
+            hipLaunchKernelGGL((k_stream<N, Q, T, false>), grid, block, 0, s->stream, S);
+        }
+        SEL_LAUNCH_CHECK();
+        return toc(s, ev);
+    }
+
     template <int MODE>
     static int launch_stage(sel_sim *s, const StageArgs<T> &A)
     {
+        if constexpr (DIM == 3 && MODE == M_STAGE23) {
+            if (s->aff) return launch_stream(s, A);
+        }
         dim3 grid((unsigned)xcd_grid(A.nblk)), block(GG::BLOCK);
         hipEvent_t ev = nullptr;
         const int kind = (MODE == M_STAGE1) ? 0 : (MODE == M_STAGE23) ? 1 : 3;
@@ -208,6 +263,18 @@ struct Impl {
                            s->p.accel[1], DIM == 3 ? s->p.accel[2] : 0.0);
         SEL_LAUNCH_CHECK();
         return SEL_OK;
+    }
+
+    // mirrored tables of the line operators (LineTab): the derivative matrix,
+    // then the modal filter minus the identity
+    static int line_tables(const Tables &t, double *out)
+    {
+        constexpr int n1 = N + 1;
+        double M[n1 * n1];
+        line_tab<n1>(t.D, out);
+        for (int q = 0; q < n1 * n1; ++q) M[q] = t.F[q] - (q % (n1 + 1) == 0 ? 1.0 : 0.0);
+        line_tab<n1>(M, out + LineTab<n1>::size);
+        return 2 * LineTab<n1>::size;
     }
 
     // one time step: collide (and filter the previous step's result) ->
@@ -523,7 +590,7 @@ struct Impl {
     static const Ops *ops()
     {
         static const Ops o = {geometry, mass, init,    step,     moments,  reduce,   scatter,
-                              gather,   apply, features, set_force, grad_row, axial_terms};
+                              gather,   apply, features, set_force, grad_row, axial_terms, line_tables};
         return &o;
     }
 };

@@ -21,6 +21,7 @@ static int ipow(int b, int e)
 }
 
 static int build_interfaces(sel_mesh *m);
+static void find_affine(sel_mesh *m);
 
 // Geometric consistency of the node numbering (the continuous element
 // coupling of Sec. 2.2 identifies the copies of a node; the wall flux of
@@ -358,6 +359,7 @@ static int mesh_create(int32_t dim, int32_t N, int64_t E, const double *xyz, con
                 used[q] = 1;
             }
         }
+        find_affine(m);
         m->dg = dg;
         if (dg) {
             if (int rc = build_interfaces(m)) {
@@ -372,6 +374,50 @@ static int mesh_create(int32_t dim, int32_t N, int64_t E, const double *xyz, con
     }
     *out = m;
     return SEL_OK;
+}
+
+// Affine elements: x = x_0 + sum_m a_m (r_m + 1), a_m half the edge from node 0
+// to the last node along r_m, at every node up to a few roundings of the
+// element's coordinates (8 units of 2^-52 of their magnitude). The metric
+// of such an element is constant up to the rounding that it has anyway when it
+// is differentiated node by node. One element off this leaves the list empty.
+static void find_affine(sel_mesh *m)
+{
+    sel::Tables t;
+    if (sel::build_gll(m->N, t)) return;
+    const int d = m->dim, n1 = m->n1, N = m->N;
+    const int str[3] = {1, n1, n1 * n1};
+    std::vector<double> out((size_t)m->E * 10, 0.0);
+    for (int64_t e = 0; e < m->E; ++e) {
+        const double *x = m->xyz.data() + e * m->np * d;
+        double a[3][3] = {}, mag = 0.0;
+        for (int r = 0; r < d; ++r)
+            for (int c = 0; c < d; ++c) a[r][c] = 0.5 * (x[(int64_t)N * str[r] * d + c] - x[c]);
+        for (int64_t q = 0; q < (int64_t)m->np * d; ++q) mag = std::max(mag, std::fabs(x[q]));
+        const double tol = 8.0 * 0x1p-52 * mag;
+        for (int p = 0; p < m->np; ++p)
+            for (int c = 0; c < d; ++c) {
+                double v = x[c];
+                for (int r = 0; r < d; ++r) v += a[r][c] * (t.xi[(p / str[r]) % n1] + 1.0);
+                if (!(std::fabs(v - x[(int64_t)p * d + c]) <= tol)) return;
+            }
+        if (d == 2) a[2][2] = 1.0;
+        // dr_m/dx = (a_{m+1} x a_{m+2}) / J
+        double cx[3][3], J = 0.0;
+        for (int r = 0; r < 3; ++r) {
+            const double *u = a[(r + 1) % 3], *v = a[(r + 2) % 3];
+            cx[r][0] = u[1] * v[2] - u[2] * v[1];
+            cx[r][1] = u[2] * v[0] - u[0] * v[2];
+            cx[r][2] = u[0] * v[1] - u[1] * v[0];
+        }
+        for (int c = 0; c < 3; ++c) J += a[0][c] * cx[0][c];
+        if (!(J > 0.0) || !std::isfinite(J)) return;
+        double *o = out.data() + 10 * e;
+        for (int r = 0; r < 3; ++r)
+            for (int c = 0; c < 3; ++c) o[3 * r + c] = cx[r][c] / J;
+        o[9] = J;
+    }
+    m->aff.swap(out);
 }
 
 // Interfaces of the discontinuous coupling: every face that is not a wall is

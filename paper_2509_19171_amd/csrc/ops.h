@@ -19,6 +19,7 @@ struct Ops {
     int (*set_force)(sel_sim *, const double *d_F);  // d_F: device FP64 [E][np][dim]
     int (*grad_row)(sel_sim *, int c, double *d_out);  // du_c/dx_q, FP64 [E][np][dim]
     int (*axial_terms)(sel_sim *, const double *n, double *d_out);  // wJ u.n and wJ, FP64 [2][E][np]
+    int (*line_tables)(const Tables &, double *);  // returns the number of values (at most kLineTab)
 };
 
 // learned-closure inference on the simulation's feature rows (closure.hip)

@@ -13,6 +13,7 @@ namespace sel {
 
 constexpr int kMaxN1 = 16;  // host tables up to N = 15
 constexpr int kMaxQ = 27;
+constexpr int kLineTab = 2 * (2 * (kMaxN1 / 2 + 1) * (kMaxN1 / 2));  // values of the two mirrored line tables at most
 
 // Host-side tables of the spectral element (built in tables.cpp).
 struct Tables {
@@ -65,6 +66,9 @@ struct sel_mesh {
     int maxm = 0;
     std::vector<int32_t> posmap;  // [E][nbe] slot of each element-boundary node
     std::vector<int32_t> hidx;    // [ngrp] index among groups with > 2 members, or -1
+    // dr_m/dx_k (9) and J of each element when every element is an affine image
+    // of the reference element up to the rounding of its coordinates, else empty
+    std::vector<double> aff;      // [E][10]
     // discontinuous coupling: no node is shared (one group per element-
     // boundary node); nbr holds, for every face node of every face that is
     // not a wall, the group of the coincident node in the element across it
@@ -80,6 +84,7 @@ struct sel_sim {
     int64_t E = 0, ngrp = 0, Gi = 0, Gtot = 0, nwall = 0;
     int64_t nstate = 0;        // entries of one state array (Q per node, groups padded to tiles of 64)
     sel_params p{};
+    sel::Tables tab;           // 1D tables (FP64)
     int prec = SEL_FP64;
     size_t tsize = 8;
     double tau = 0, omega = 0;
@@ -92,6 +97,8 @@ struct sel_sim {
     double time = 0.0;
     int64_t nstep = 0;
     // device pointers (typed views of the workspace)
+    void *tabL = nullptr;      // T: mirrored line tables (LineTab), derivative then filter - identity
+    void *aff = nullptr;       // T [E][10]: dr_m/dx_k and J of each element when all are affine, else nullptr
     void *tabD = nullptr, *tabF = nullptr, *tabW = nullptr;  // T tables [n1*n1], [n1*n1], [n1]
     double *geoD = nullptr, *geoW = nullptr;                  // FP64 D-hat and GLL weights
     int32_t *pcode = nullptr, *bpos = nullptr;
