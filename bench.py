@@ -62,17 +62,19 @@ def method_bytes(dim, Q, s):
     return {"stage1": s * (2 + geo), "later_stage": s * (3 + geo), "step": s * (8 + 3 * geo)}
 
 
-def algorithmic_bytes(info, Q, s):
+def algorithmic_bytes(info, Q, s, affine=False):
     """Per step: the method's bytes (method_bytes) times the node-velocities.
     Per launch, this implementation's own count of what each kernel must move
     at least, every value once:
       stage1   read the operand and write the post-collision state at every
-               unique node, write the density, write interior results and
-               the boundary-node element contributions, read the metric;
+               unique node, write the density (2D, where the first stage
+               streams in the same kernel: also write interior results and
+               the boundary-node element contributions, read the metric);
       stage23  read the operand at every unique node, read the post-collision
                state and write the result at interior nodes, write the
                boundary-node contributions, read the metric, the interior
-               inverse mass and density;
+               inverse mass and density (none of the three on a 3D mesh of
+               affine elements, ``affine``);
       assembly read the contributions, read two states and write one at every
                node group, read the group mass and density and the member
                lists (4-byte ints);
@@ -85,8 +87,8 @@ def algorithmic_bytes(info, Q, s):
     nv = E * npn * Q
     step = method_bytes(dim, Q, s)["step"] * nv
     per = {
-        "stage1": s * (2 * Q * G + G + Q * E * ni + Q * E * nb + E * npn * dim * dim),
-        "stage23": s * (Q * G + 2 * Q * E * ni + Q * E * nb + E * npn * dim * dim + 2 * E * ni),
+        "stage1": s * (2 * Q * G + G + (Q * E * npn + E * npn * dim * dim if dim == 2 else 0)),
+        "stage23": s * (Q * G + 2 * Q * E * ni + Q * E * nb + (0 if affine else E * npn * dim * dim + 2 * E * ni)),
         "assembly": s * (Q * E * nb + 3 * Q * ng + 2 * ng) + 4 * (E * nb + ng),
         "filter": s * 2 * Q * G,
         # closure: read the state at every unique node and the metric, write 6 features per node id
@@ -241,7 +243,7 @@ def time_config(name, case, precision, steps, warmup, torch, closure=None, hbm=T
     f = time_form(case, precision, steps, warmup, torch, closure=closure)
     info = f["info"]
     s = 4 if precision.startswith("fp32") else 8
-    nv, step_bytes, per = algorithmic_bytes(info, case.Q, s)
+    nv, step_bytes, per = algorithmic_bytes(info, case.Q, s, affine=True)
     if closure is not None:
         step_bytes += per["features"] + per["network"]
     out = {"workload": name, "precision": precision + ("+closure" if closure is not None else ""),
@@ -371,7 +373,7 @@ def main():
     head = forms[args.precision]
     info = head["info"]
     s = 4 if args.precision == "fp32dev" else 8
-    nv, step_bytes, per_kind = algorithmic_bytes(info, case.Q, s)
+    nv, step_bytes, per_kind = algorithmic_bytes(info, case.Q, s, affine=True)
     value = nv / (head["ms_per_step"] * 1e-3) / 1e9
     kern = head["kernels"]
     avg = {k: v[0] / v[1] for k, v in kern.items() if v[1]}

@@ -155,7 +155,7 @@ int sel_init(const sel_mesh *mesh, const sel_params *p, const double *rho, const
  * Sec. 2.2: BGK collision with F** (Sec. 2.1, Eqs. perfect1-perfect2), the
  * streaming operator with F* and the wall flux integrated over dt by the
  * chosen Runge-Kutta form (Sec. 2.2, 2.2.1, 2.2.2), then the modal filter
- * (Sec. 2.2.3; applied lazily: fused into the next step's first stage, or
+ * (Sec. 2.2.3; applied lazily: ahead of the next step's collision, or
  * run at the end of the call, so the state seen after the call is filtered).
  * Errors: SEL_EINVAL (null sim or nsteps < 0), SEL_EDEVICE (launch failure);
  * device faults and non-finite states surface at the next synchronising call. */
@@ -164,8 +164,8 @@ int sel_step(sel_sim *sim, int64_t nsteps);
 /* Same as sel_step, with HIP events recorded on the stream around every
  * kernel launch. On return (it synchronises) ms[k] holds the summed device
  * time and launches[k] the number of launches of kernel kind k:
- *   0 first-stage element kernel (filter of the previous step, collision,
- *     streaming operator), 1 later-stage element kernel (streaming operator),
+ *   0 filter of the previous step and collision (2D: first-stage kernel, which
+ *     also streams), 1 streaming operator of a stage (2D: of the later stages),
  *   2 shared-node assembly, 3 end-of-call filter, 4 closure features,
  *   5 closure network (both only with a closure attached). ms and launches
  *   hold SEL_NKIND entries. */

@@ -135,10 +135,11 @@ __device__ __forceinline__ T edot(T x, T y, T z)
 
 // BGK collision with the higher-order force F** (Sec. 2.1): from the node's
 // values v[a] (full f, or the deviation g = f - t_a rho0 when DEV) compute
-// rho, u = sum e f / rho, F = rho g and
+// rho, u = sum e f / rho, F = rho g (+ Fn when fn is set) and
 //   f* = f - omega (f - (f^eq - dt F**/2)) + dt F**,  omega = 1 / (tau + 1/2).
 template <int DIM, int Q, typename T, bool DEV>
-__device__ __forceinline__ void collide_node(T (&v)[Q], T rho0, T omega, T dt, const T (&g)[3], T &rho_out)
+__device__ __forceinline__ void collide_node(T (&v)[Q], T rho0, T omega, T dt, const T (&g)[3], T &rho_out, const T (&Fn)[3],
+                                             bool fn)
 {
     T m0 = 0, j0 = 0, j1 = 0, j2 = 0;
     static_for<0, Q>([&](auto A) {
@@ -151,7 +152,7 @@ __device__ __forceinline__ void collide_node(T (&v)[Q], T rho0, T omega, T dt, c
     const T rho = DEV ? rho0 + m0 : m0;
     const T inv = T(1) / rho;
     const T u0 = j0 * inv, u1 = j1 * inv, u2 = j2 * inv;
-    const T F0 = rho * g[0], F1 = rho * g[1], F2 = rho * g[2];
+    const T F0 = rho * g[0] + Fn[0], F1 = rho * g[1] + Fn[1], F2 = rho * g[2] + Fn[2];
     const T uu = u0 * u0 + u1 * u1 + u2 * u2;
     const T uF = u0 * F0 + u1 * F1 + u2 * F2;
     const T c1 = T(3), c2 = T(4.5), c3 = T(1.5);  // 1/cs2, 1/(2 cs4), 1/(2 cs2)
@@ -184,7 +185,7 @@ __device__ __forceinline__ void collide_node(T (&v)[Q], T rho0, T omega, T dt, c
         T base[Q];
         T S0 = 0, S1x = 0, S1y = 0, S1z = 0;
         // without a body force F** vanishes: the same values without its terms
-        const bool forced = (g[0] != T(0)) | (g[1] != T(0)) | (g[2] != T(0));
+        const bool forced = fn | (g[0] != T(0)) | (g[1] != T(0)) | (g[2] != T(0));
         const T c3uu = c3 * uu;
         auto pass1 = [&](auto FORCED) {
             static_for<0, Q>([&](auto A) {
@@ -685,7 +686,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
         if (valid) {
             T om = A.omega;
             if (A.dtau) om = T(1) / (A.tau + T(A.dtau[gix]) + T(0.5));
-            collide_node<DIM, Q, T, DEV>(fq, A.rho0, om, A.dt, A.g, rho);
+            collide_node<DIM, Q, T, DEV>(fq, A.rho0, om, A.dt, A.g, rho, {T(0), T(0), T(0)}, false);
             if (own) {
                 static_for<0, Q>([&](auto AA) {
                     constexpr int a = decltype(AA)::value;

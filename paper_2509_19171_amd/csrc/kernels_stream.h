@@ -177,6 +177,7 @@ struct StreamArgs {
     T ca, cb, cc, rho0;
     int incr;       // ca + cb = 1: increment form (rk_combine)
     int body;       // some pf is not zero
+    int same;       // f0in is op: read once
     T w[N + 1];     // GLL weights
     int32_t pa[NPAIR], pb[NPAIR];  // velocities of each pair, e_pb = -e_pa
     T pe[NPAIR][3], pt[NPAIR], pf[NPAIR];  // e, weight and F* per unit density of pa
@@ -282,21 +283,21 @@ __global__ void __launch_bounds__((StreamGeo<N, Q, T>::BLOCK), (sizeof(T) == 4 &
         asm volatile("" : "+v"(ln));
         const T *q = A.op + (ib + a * (uint32_t)NI), *z = A.f0in + (ib + a * (uint32_t)NI);
         const T *qb = A.op + (A.QGi + a * (uint32_t)kTile);
+        auto interior = [&](const T *p, T (&v)[NIR * VW]) {
 #pragma unroll
-        for (int r = 0; r < NIR; ++r) {
-            const uint32_t s = min(ln + NL * r, (uint32_t)(NI / VW) - 1);
-            if constexpr (VW > 1) {
-                const vec x = __builtin_nontemporal_load(reinterpret_cast<const vec *>(q) + s);
+            for (int r = 0; r < NIR; ++r) {
+                const uint32_t s = min(ln + NL * r, (uint32_t)(NI / VW) - 1);
+                if constexpr (VW > 1) {
+                    const vec x = __builtin_nontemporal_load(reinterpret_cast<const vec *>(p) + s);
 #pragma unroll
-                for (int c = 0; c < VW; ++c) V.vi[r * VW + c] = x[c];
-                const vec y = __builtin_nontemporal_load(reinterpret_cast<const vec *>(z) + s);
-#pragma unroll
-                for (int c = 0; c < VW; ++c) V.f0[r * VW + c] = y[c];
-            } else {
-                V.vi[r] = q[s];
-                V.f0[r] = __builtin_nontemporal_load(z + s);
+                    for (int c = 0; c < VW; ++c) v[r * VW + c] = x[c];
+                } else {
+                    v[r] = __builtin_nontemporal_load(p + s);
+                }
             }
-        }
+        };
+        interior(q, V.vi);
+        if (!A.same) interior(z, V.f0);
 #pragma unroll
         for (int r = 0; r < NBR; ++r) V.vb[r] = qb[tile_at<Q>(grp[r])];
     };
@@ -367,7 +368,8 @@ __global__ void __launch_bounds__((StreamGeo<N, Q, T>::BLOCK), (sizeof(T) == 4 &
                 T L = R1[ip[r * VW + v]];
                 if (A.body) L += pf * A.rhoc[id];
                 if (A.Fn) L += t3 * (ex * A.Fn[3 * id] + ey * A.Fn[3 * id + 1] + ez * A.Fn[3 * id + 2]);
-                y[v] = rk_combine(A.ca, A.cb, A.cc, V.f0[r * VW + v], V.vi[r * VW + v], L, A.incr);
+                y[v] = rk_combine(A.ca, A.cb, A.cc, A.same ? V.vi[r * VW + v] : V.f0[r * VW + v], V.vi[r * VW + v], L,
+                                  A.incr);
             }
             if constexpr (VW > 1) __builtin_nontemporal_store(y, reinterpret_cast<vec *>(o) + s);
             else o[s] = y[0];

@@ -4,6 +4,7 @@
 #include "kernels_big.h"
 #include "kernels_impl.h"
 #include "kernels_mfma.h"
+#include "kernels_relax.h"
 #include "kernels_stream.h"
 #include "ops.h"
 
@@ -141,6 +142,7 @@ struct Impl {
         S.cc = A.cc;
         S.rho0 = A.rho0;
         S.incr = A.incr;
+        S.same = A.f0in == A.op;
         S.tab = static_cast<const T *>(s->tabL);
         S.aff = static_cast<const T *>(s->aff);
         for (int i = 0; i <= N; ++i) S.w[i] = T(s->tab.w[i]);
@@ -168,9 +170,59 @@ struct Impl {
         return toc(s, ev);
     }
 
+    // 3D: the state S (filtered first when `filter`) collided into out, or with
+    // collide = false only filtered
+    static int launch_relax(sel_sim *s, const T *S, T *out, bool filter, bool collide, const float *dtau, bool force)
+    {
+        using RG = RelaxGeo<N, Q, T>;
+        RelaxArgs<T> A{};
+        A.op = S;
+        A.out = out;
+        A.rhoc = static_cast<T *>(s->rhoc);
+        A.tab = static_cast<const T *>(s->tabL) + LineTab<N + 1>::size;
+        A.Fn = force ? static_cast<const T *>(s->Fn) : nullptr;
+        A.dtau = dtau;
+        A.bpos = s->bpos;
+        A.bmap = s->bmap;
+        A.bown = s->bown;
+        A.E = s->E;
+        A.Gi = s->Gi;
+        A.Gtot = s->Gtot;
+        A.QGi = (int64_t)Q * s->Gi;
+        A.dt = T(s->p.dt);
+        A.omega = T(s->omega);
+        A.tau = T(s->tau);
+        A.rho0 = T(s->p.rho0);
+        for (int q = 0; q < 3; ++q) A.g[q] = T(s->p.accel[q]);
+        hipEvent_t ev = nullptr;
+        if (int rc = tic(s, collide ? 0 : 3, ev)) return rc;
+        const int64_t nb = (s->E + RG::EPB - 1) / RG::EPB;
+        if (filter && RG::FUSED) {
+            const dim3 grid((unsigned)xcd_grid(nb)), block(RG::BLOCK);
+            if constexpr (RG::FUSED) {
+                if (collide) hipLaunchKernelGGL((k_relax<N, Q, T, DEV, true>), grid, block, 0, s->stream, A);
+                else hipLaunchKernelGGL((k_relax<N, Q, T, DEV, false>), grid, block, 0, s->stream, A);
+            }
+        } else {
+            if constexpr (!RG::FUSED) {
+                if (filter) {
+                    hipLaunchKernelGGL((k_filter<N, Q, T>), dim3((unsigned)xcd_grid(s->E)),
+                                       dim3(FilterGeo<N, Q, T>::BLOCK), 0, s->stream, A);
+                    A.op = A.out;
+                }
+            }
+            if (collide)
+                hipLaunchKernelGGL((k_collide<N, Q, T, DEV>), dim3((unsigned)((s->Gtot + 255) / 256)), dim3(256), 0,
+                                   s->stream, A);
+        }
+        SEL_LAUNCH_CHECK();
+        return toc(s, ev);
+    }
+
     template <int MODE>
     static int launch_stage(sel_sim *s, const StageArgs<T> &A)
     {
+        static_assert(DIM == 2 || MODE == M_STAGE23 || MODE == M_LOCAL, "3D: launch_relax");
         if constexpr (DIM == 3 && MODE == M_STAGE23) {
             if (s->aff) return launch_stream(s, A);
         }
@@ -183,7 +235,7 @@ struct Impl {
                 return SEL_EUNSUPPORTED;
             }
             if (int rc = tic(s, kind, ev)) return rc;
-            hipLaunchKernelGGL((k_stage_big<N, Q, T, DEV, MODE>), grid, dim3(BigGeo<N>::BLOCK), 0, s->stream, A);
+            hipLaunchKernelGGL((k_stage_big<N, Q, T, MODE>), grid, dim3(BigGeo<N>::BLOCK), 0, s->stream, A);
         } else {
             if (int rc = tic(s, kind, ev)) return rc;
             // element contributions under the discontinuous coupling carry the
@@ -340,6 +392,10 @@ struct Impl {
     static int stage_one(sel_sim *s, StageArgs<T> &A, GroupArgs<T> &B, const T *S, T *F0, T *FA, double cc,
                          bool pending)
     {
+        if constexpr (DIM == 3) {
+            if (int rc = launch_relax(s, S, F0, pending, true, A.dtau, s->force_on)) return rc;
+            return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
+        } else {
         A.op = S;
         A.f0out = F0;
         A.out = FA;
@@ -365,6 +421,7 @@ struct Impl {
         B.cb = T(1);
         B.cc = T(cc);
         return launch_group(s, B);
+        }
     }
 
     // The four printed stage formulas of Sec. 2.2.2 with L applied linearly
@@ -437,9 +494,13 @@ struct Impl {
             s->nstep += 1;
         }
         if (pending) {
-            A.op = st(s, s->cur);
-            A.out = st(s, s->cur ^ 1);
-            if (int rc = launch_stage<M_FILTER>(s, A)) return rc;
+            if constexpr (DIM == 3) {
+                if (int rc = launch_relax(s, st(s, s->cur), st(s, s->cur ^ 1), true, false, nullptr, false)) return rc;
+            } else {
+                A.op = st(s, s->cur);
+                A.out = st(s, s->cur ^ 1);
+                if (int rc = launch_stage<M_FILTER>(s, A)) return rc;
+            }
             s->cur ^= 1;
         }
         return SEL_OK;
@@ -511,6 +572,11 @@ struct Impl {
             B.cc = T(1);
             return launch_group(s, B);
         }
+        if constexpr (DIM == 3) {
+            if (op == SEL_OP_COLLIDE) return launch_relax(s, src, dst, false, true, nullptr, false);
+            if (op == SEL_OP_FILTER) return launch_relax(s, src, dst, true, false, nullptr, false);
+            return SEL_EINVAL;
+        } else {
         if (op == SEL_OP_COLLIDE) {
             A.f0out = dst;
             A.out = st(s, s->cur ^ 1);
@@ -523,6 +589,7 @@ struct Impl {
             return launch_stage<M_FILTER>(s, A);
         }
         return SEL_EINVAL;
+        }
     }
 
     // closure features of the current state: one row per node id
