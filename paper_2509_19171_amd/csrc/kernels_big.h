@@ -178,7 +178,12 @@ __global__ void __launch_bounds__(BigGeo<N>::BLOCK) k_stage_big(StageArgs<T> A)
                 T f0v;
                 if constexpr (PF) f0v = f0[r];
                 else f0v = A.f0in[si[r].base + (int64_t)a * si[r].stride];
-                const T L = rt * invw[r] + A.fsc[a] * rho[r];
+                T L = rt * invw[r] + A.fsc[a] * rho[r];
+                if (A.Fn) {
+                    const T *F = A.Fn + 3 * gix[r];
+                    L += T(3.0 * lat_t<DIM, Q>(a)) *
+                         edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(F[0], F[1], F[2]);
+                }
                 A.out[si[r].base + (int64_t)a * si[r].stride] = rk_combine(A.ca, A.cb, A.cc, f0v, v[r], L, A.incr);
             } else if constexpr (!rest) {
                 // the assembly takes the rest velocity's contributions as zero

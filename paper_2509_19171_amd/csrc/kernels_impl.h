@@ -380,6 +380,7 @@ struct StageArgs {
     T tau;                // relaxation time
     const float *dtau;    // learned-closure increments per node id (nullptr: plain method)
     const int32_t *nbr;   // discontinuous coupling: [E][2 dim][(N+1)^(dim-1)] group across each face (nullptr: continuous)
+    const T *Fn;          // force density per node id [Gtot][3], added to rho g (nullptr: none)
     int collide_only;     // M_STAGE1: stop after writing the post-collision state
 };
 
@@ -682,11 +683,16 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     }
 
     T rho = 0;
+    T Fv[3] = {T(0), T(0), T(0)};
+    if (A.Fn && valid) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) Fv[c] = A.Fn[3 * gix + c];
+    }
     if constexpr (MODE == M_STAGE1) {
         if (valid) {
             T om = A.omega;
             if (A.dtau) om = T(1) / (A.tau + T(A.dtau[gix]) + T(0.5));
-            collide_node<DIM, Q, T, DEV>(fq, A.rho0, om, A.dt, A.g, rho, {T(0), T(0), T(0)}, false);
+            collide_node<DIM, Q, T, DEV>(fq, A.rho0, om, A.dt, A.g, rho, Fv, A.Fn != nullptr);
             if (own) {
                 static_for<0, Q>([&](auto AA) {
                     constexpr int a = decltype(AA)::value;
@@ -766,6 +772,12 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     // LDS, v and f0v the node's operand and post-collision values
     auto velocity = [&](auto AA, const T *P, T v, T f0v) {
         constexpr int a = decltype(AA)::value;
+        // L at an interior node: volume term over the mass, and F*
+        auto total = [&](T rt) {
+            T L = rt * invw + A.fsc[a] * rho;
+            if (A.Fn) L += T(3.0 * lat_t<DIM, Q>(a)) * edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(Fv[0], Fv[1], Fv[2]);
+            return L;
+        };
         T rt = stream_volume<DIM, N, Q, a, DIF>(P, v, Di, Dj, Dk, Gr, rowr, rows, rowt);
         if (wcode) {
             constexpr int b = lat_opp<DIM, Q>(a);
@@ -780,15 +792,14 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
         }
         if constexpr (STG) {
             // kept in the register of the consumed operand, stored after the loop
-            if (inner) fq[a] = rk_combine(A.ca, A.cb, A.cc, f0v, v, rt * invw + A.fsc[a] * rho, A.incr);
+            if (inner) fq[a] = rk_combine(A.ca, A.cb, A.cc, f0v, v, total(rt), A.incr);
             else fq[a] = rt;
         } else if (valid) {
             if constexpr (MODE == M_LOCAL) {
                 A.local[((int64_t)a * A.E + e) * NP + p] = rt;
             } else {
                 if (inner) {
-                    const T L = rt * invw + A.fsc[a] * rho;
-                    A.out[si.base + (int64_t)a * si.stride] = rk_combine(A.ca, A.cb, A.cc, f0v, v, L, A.incr);
+                    A.out[si.base + (int64_t)a * si.stride] = rk_combine(A.ca, A.cb, A.cc, f0v, v, total(rt), A.incr);
                 } else {
                     A.rtb[(int64_t)a * A.plane + slot] = rt;
                 }
@@ -918,6 +929,7 @@ struct GroupArgs {
     T ca, cb, cc;
     int incr;  // ca + cb = 1 (time steps): FP32 increment form
     T fsc[kMaxQ];
+    const T *Fn;  // force density per node id [Gtot][3], added to rho g (nullptr: none)
     // discontinuous coupling (k_group_split with DGN = N): interface table, face
     // tags, node index of each boundary slot and the metric
     const int32_t *nbr, *ftag, *bpos;
@@ -932,14 +944,13 @@ struct GroupArgs {
 // element-boundary node (group id e * NB + b) and the upwind flux of its
 // interface faces (with the stage value fk across each face) is added to its
 // contribution before the mass.
-// The velocities of each group are split between two wavefronts: waves 2k
-// and 2k + 1 of a workgroup take the lower and upper velocities of the same
-// 64 groups (uniform in each wavefront), so a thread holds half the values
-// and twice the groups are in flight per CU; the arithmetic of a velocity
-// does not depend on the split.
+// The velocities of each group are split between SPLIT wavefronts of a
+// workgroup (uniform in each wavefront), so a thread holds 1/SPLIT of the values
+// and more loads are in flight; the arithmetic of a velocity does not depend on
+// the split.
 template <int A0, int A1, int Q, typename T, int DGN>
 __device__ __forceinline__ void group_range(const GroupArgs<T> &A, int64_t g, int nm, int64_t h, T invM, T rho,
-                                            SIdx si)
+                                            const T (&F)[3], SIdx si)
 {
     // every load of the group is issued before its first store (the output
     // may alias the inputs as far as the compiler knows, which would
@@ -1025,31 +1036,43 @@ __device__ __forceinline__ void group_range(const GroupArgs<T> &A, int64_t g, in
     static_for<A0, A1>([&](auto AA) {
         constexpr int a = decltype(AA)::value, u = a - A0;
         const int64_t ix = si.base + (int64_t)a * si.stride;
-        const T L = sum[u] * invM + A.fsc[a] * rho;
+        T L = sum[u] * invM + A.fsc[a] * rho;
+        if (A.Fn) {
+            constexpr int DIM = (Q == 9) ? 2 : 3;
+            L += T(3.0 * lat_t<DIM, Q>(a)) *
+                 edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(F[0], F[1], F[2]);
+        }
         A.out[ix] = rk_combine(A.ca, A.cb, A.cc, v0[u], vk[u], L, A.incr);
     });
 }
 
-template <int Q, typename T, int DGN = 0>
+template <int Q, typename T, int SPLIT, int DGN = 0>
 __global__ void __launch_bounds__(256) k_group_split(GroupArgs<T> A)
 {
+    constexpr int GPB = 256 / SPLIT;  // groups per workgroup
     const int w = threadIdx.x >> 6;
-    // blocks of 128 groups, a contiguous range of them per XCD: groups are
+    // blocks of GPB groups, a contiguous range of them per XCD: groups are
     // ordered by owner element, so each XCD assembles the groups of the
     // elements it streams, and the next stage finds them in its own L2
-    const int64_t nb = (A.ngrp + 127) / 128;
+    const int64_t nb = (A.ngrp + GPB - 1) / GPB;
     const int64_t gb = xcd_block(nb);
     if (gb >= nb) return;  // whole workgroup
-    const int64_t g = gb * 128 + (w >> 1) * 64 + (threadIdx.x & 63);
+    const int64_t g = gb * GPB + (w / SPLIT) * 64 + (threadIdx.x & 63);
     if (g >= A.ngrp) return;
     const int nm = A.goff[g + 1] - A.goff[g];
-    const int64_t h = (nm > 2) ? (int64_t)A.hidx[g] : 0;
+    const int64_t h = A.hidx[g];  // (-1 with two members or fewer, then unused)
+    T F[3] = {T(0), T(0), T(0)};
+    if (A.Fn) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) F[c] = A.Fn[3 * (A.Gi + g) + c];
+    }
     const T invM = A.invMb[g];
     const T rho = A.rhoc[A.Gi + g];
     const SIdx si = sidx_group(g, Q, A.QGi);
-    constexpr int HQ = (Q + 1) / 2;
-    if (w & 1) group_range<HQ, Q, Q, T, DGN>(A, g, nm, h, invM, rho, si);
-    else group_range<0, HQ, Q, T, DGN>(A, g, nm, h, invM, rho, si);
+    static_for<0, SPLIT>([&](auto WW) {
+        constexpr int k = decltype(WW)::value;
+        if (w % SPLIT == k) group_range<k * Q / SPLIT, (k + 1) * Q / SPLIT, Q, T, DGN>(A, g, nm, h, invM, rho, F, si);
+    });
 }
 
 // ------------------------------------------------------ closure features --
@@ -1433,10 +1456,8 @@ __global__ void k_gather_plane(NodeMap M, const T *src, double *dst, int a, doub
 
 // ------------------------------------------------------ per-node force --
 // A force density per node F_n is added to rho g (Sec. 2.1; F = rho g + F_n,
-// taken at the collision and frozen for the stages). Both force terms are
-// linear in F, so the per-node part is applied by two passes over the node
-// ids beside the kernels of the body force: F** after the collision, F*
-// after each stage's assembly.
+// taken at the collision and frozen for the stages): F** in the collision and
+// F* in every update, as the body force's.
 
 // state index of node id q (interior ids first, then the groups)
 __device__ __forceinline__ SIdx sidx_node(int64_t q, int64_t Gi, int NI, int Q, int64_t QGi)
@@ -1466,61 +1487,6 @@ __global__ void k_force_set(NodeMap M, const double *F, int dim, T *Fn)
         id = M.Gi + M.bmap[e * M.NB + b];
     }
     for (int k = 0; k < 3; ++k) Fn[id * 3 + k] = k < dim ? T(F[q * dim + k]) : T(0);
-}
-
-// after the collision: f*_a += (1 - omega/2) dt F**_a(u, F_n), with
-// F**_a = t_a ((e.u)(e.F)/cs4 - (u.F)/cs2) and u = j / rho of the
-// post-collision state (the collision and F** of rho g leave j unchanged)
-template <int DIM, int Q, typename T, bool DEV>
-__global__ void k_force_collide(T *f, const T *Fn, const float *dtau, int64_t Gtot, int64_t Gi, int NI,
-                                int64_t QGi, T tau, T dt, T rho0)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= Gtot) return;
-    const SIdx si = sidx_node(q, Gi, NI, Q, QGi);
-    T v[Q];
-    T m0 = 0, j0 = 0, j1 = 0, j2 = 0;
-    static_for<0, Q>([&](auto AA) {
-        constexpr int a = decltype(AA)::value;
-        v[a] = f[si.base + (int64_t)a * si.stride];
-        m0 += v[a];
-        if constexpr (lat_e<DIM, Q>(a, 0) != 0) j0 += T(lat_e<DIM, Q>(a, 0)) * v[a];
-        if constexpr (lat_e<DIM, Q>(a, 1) != 0) j1 += T(lat_e<DIM, Q>(a, 1)) * v[a];
-        if constexpr (lat_e<DIM, Q>(a, 2) != 0) j2 += T(lat_e<DIM, Q>(a, 2)) * v[a];
-    });
-    const T rho = DEV ? rho0 + m0 : m0;
-    const T u0 = j0 / rho, u1 = j1 / rho, u2 = j2 / rho;
-    const T F0 = Fn[q * 3], F1 = Fn[q * 3 + 1], F2 = Fn[q * 3 + 2];
-    const T uF = u0 * F0 + u1 * F1 + u2 * F2;
-    const T omega = T(1) / (tau + (dtau ? T(dtau[q]) : T(0)) + T(0.5));
-    const T coef = (T(1) - T(0.5) * omega) * dt;
-    static_for<0, Q>([&](auto AA) {
-        constexpr int a = decltype(AA)::value;
-        constexpr int ex = lat_e<DIM, Q>(a, 0), ey = lat_e<DIM, Q>(a, 1), ez = lat_e<DIM, Q>(a, 2);
-        const T t = T(lat_t<DIM, Q>(a));
-        const T eu = T(ex) * u0 + T(ey) * u1 + T(ez) * u2;
-        const T eF = T(ex) * F0 + T(ey) * F1 + T(ez) * F2;
-        f[si.base + (int64_t)a * si.stride] = v[a] + coef * (t * (T(9) * eu * eF - T(3) * uF));
-    });
-}
-
-// after a stage out = ca f0 + cb fk + cc L(fk): out_a += cc F*_a(F_n),
-// F*_a = t_a (e_a . F) / cs2
-template <int DIM, int Q, typename T>
-__global__ void k_force_stage(T *out, const T *Fn, int64_t Gtot, int64_t Gi, int NI, int64_t QGi, T cc)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= Gtot) return;
-    const SIdx si = sidx_node(q, Gi, NI, Q, QGi);
-    const T F0 = Fn[q * 3], F1 = Fn[q * 3 + 1], F2 = Fn[q * 3 + 2];
-    static_for<0, Q>([&](auto AA) {
-        constexpr int a = decltype(AA)::value;
-        constexpr int ex = lat_e<DIM, Q>(a, 0), ey = lat_e<DIM, Q>(a, 1), ez = lat_e<DIM, Q>(a, 2);
-        if constexpr (ex != 0 || ey != 0 || ez != 0) {
-            const T t = T(lat_t<DIM, Q>(a));
-            out[si.base + (int64_t)a * si.stride] += cc * (t * T(3) * (T(ex) * F0 + T(ey) * F1 + T(ez) * F2));
-        }
-    });
 }
 
 // moments (Eqs. pressure, momentum) in FP64 at every element node

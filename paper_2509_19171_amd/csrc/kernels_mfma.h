@@ -66,6 +66,7 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
     __shared__ __attribute__((aligned(16))) float pl[PLN];
     __shared__ float xb[8][2][128];  // per wavefront: r- and s-derivatives of a velocity pair
     __shared__ float sfs[Q];  // F* per unit density of each velocity
+    __shared__ float sfe[Q][3];  // 3 t_a e_a (force per node)
 
     const int tid = threadIdx.x;
     const int64_t e = xcd_block(A.nblk);
@@ -80,7 +81,12 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
     const int64_t ib = e * (int64_t)Q * NI;
     static_for<0, Q>([&](auto AA) {
         constexpr int a = decltype(AA)::value;
-        if (tid == a) sfs[a] = A.fsc[a];
+        if (tid == a) {
+            sfs[a] = A.fsc[a];
+            sfe[a][0] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, 0));
+            sfe[a][1] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, 1));
+            sfe[a][2] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, 2));
+        }
     });
 
     // ------------------------------------------------------------ loads --
@@ -257,6 +263,16 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
                 } else {
                     const mf4 rt = *reinterpret_cast<const mf4 *>(pl + (a - 1) * NP + s0);
                     L = rt * iw4[s0 / 4] + fs * rh;
+                }
+                if (A.Fn) {
+                    // [4 slots][3] as three vectors
+                    const mf4 *F4 = reinterpret_cast<const mf4 *>(A.Fn + 3 * (e * NI + s0));
+                    const mf4 u = F4[0], v = F4[1], x = F4[2];
+                    const float e0 = sfe[a][0], e1 = sfe[a][1], e2 = sfe[a][2];
+                    L[0] += e0 * u[0] + e1 * u[1] + e2 * u[2];
+                    L[1] += e0 * u[3] + e1 * v[0] + e2 * v[1];
+                    L[2] += e0 * v[2] + e1 * v[3] + e2 * x[0];
+                    L[3] += e0 * x[1] + e1 * x[2] + e2 * x[3];
                 }
                 const mf4 fk = fkv[r];
                 const mf4 f0 = f0v[r];

@@ -129,7 +129,7 @@ struct Impl {
         S.rtb = A.rtb;
         S.rhoc = A.rhoc;
         S.wallu = A.wallu;
-        S.Fn = nullptr;
+        S.Fn = A.Fn;
         S.bpos = A.bpos;
         S.bmap = A.bmap;
         S.posmap = A.posmap;
@@ -268,12 +268,20 @@ struct Impl {
         hipEvent_t ev = nullptr;
         if (int rc = tic(s, 2, ev)) return rc;
         // the discontinuous coupling adds its interface flux here
-        // 128 groups per workgroup, two wavefronts per group
-        dim3 grid2((unsigned)xcd_grid((s->ngrp + 127) / 128));
+        // wavefronts per 64 groups: four fill the chip sooner on small meshes
+        // (D3Q27 FP32, us with 2 and 4: 8^3 elements N = 3 10.8 and 7.9, 1024
+        // elements N = 5 13.9 and 10.6, 16^3 N = 7 55 and 53.5); two where the
+        // memory is the limit and a thread's values are few loads anyway: FP64
+        // (12^3 N = 7 46.4 and 47.4) and the discontinuous coupling, which looks
+        // up its faces per thread (10^3 N = 5 15.6 and 17.8)
+        const bool two = B.nbr || (sizeof(T) == 8 && s->ngrp > (1 << 17));
+        const dim3 grid((unsigned)xcd_grid((s->ngrp * (two ? 2 : 4) + 255) / 256));
         if (B.nbr) {
-            hipLaunchKernelGGL((k_group_split<Q, T, N>), grid2, block, 0, s->stream, B);
+            hipLaunchKernelGGL((k_group_split<Q, T, 2, N>), grid, block, 0, s->stream, B);
+        } else if (two) {
+            hipLaunchKernelGGL((k_group_split<Q, T, 2>), grid, block, 0, s->stream, B);
         } else {
-            hipLaunchKernelGGL((k_group_split<Q, T>), grid2, block, 0, s->stream, B);
+            hipLaunchKernelGGL((k_group_split<Q, T, 4>), grid, block, 0, s->stream, B);
         }
         SEL_LAUNCH_CHECK();
         return toc(s, ev);
@@ -342,26 +350,6 @@ struct Impl {
         return SEL_OK;
     }
 
-    // its F** part on the post-collision state f
-    static int force_collide(sel_sim *s, T *f, const float *dtau)
-    {
-        hipLaunchKernelGGL((k_force_collide<DIM, Q, T, DEV>), dim3((unsigned)((s->Gtot + 255) / 256)), dim3(256), 0,
-                           s->stream, f, static_cast<const T *>(s->Fn), dtau, s->Gtot, s->Gi, NI, (int64_t)Q * s->Gi,
-                           T(s->tau), T(s->p.dt), T(s->p.rho0));
-        SEL_LAUNCH_CHECK();
-        return SEL_OK;
-    }
-
-    // its F* part of a stage: out += cc F*(F_n)
-    static int force_stage(sel_sim *s, T *out, double cc)
-    {
-        hipLaunchKernelGGL((k_force_stage<DIM, Q, T>), dim3((unsigned)((s->Gtot + 255) / 256)), dim3(256), 0,
-                           s->stream, out, static_cast<const T *>(s->Fn), s->Gtot, s->Gi, NI, (int64_t)Q * s->Gi,
-                           T(cc));
-        SEL_LAUNCH_CHECK();
-        return SEL_OK;
-    }
-
     // One element pass and its assembly: out = ca f0 + cb fk + cc L(fk).
     static int stage_pass(sel_sim *s, StageArgs<T> &A, GroupArgs<T> &B, const T *fk, const T *f0, T *out,
                           double ca, double cb, double cc)
@@ -379,16 +367,15 @@ struct Impl {
         B.ca = T(ca);
         B.cb = T(cb);
         B.cc = T(cc);
-        if (int rc = launch_group(s, B)) return rc;
-        return s->force_on ? force_stage(s, out, cc) : SEL_OK;
+        return launch_group(s, B);
     }
 
     // First stage: filter (when pending) and collide the state S into the
-    // post-collision state y = F0, then FA = y + cc L(y). The continuous
-    // coupling streams in the same kernel (a shared node's post-collision
-    // value is the same in every element); the discontinuous coupling needs
-    // the post-collision values across faces, and a per-node force adds its
-    // F** part to y first, so both stream in a second pass.
+    // post-collision state y = F0, then FA = y + cc L(y). 3D: the relaxation,
+    // then a streaming pass like the later stages'. 2D: the continuous coupling
+    // streams in the same kernel (a shared node's post-collision value is the
+    // same in every element); the discontinuous coupling needs the
+    // post-collision values across faces and streams in a second pass.
     static int stage_one(sel_sim *s, StageArgs<T> &A, GroupArgs<T> &B, const T *S, T *F0, T *FA, double cc,
                          bool pending)
     {
@@ -403,14 +390,11 @@ struct Impl {
         A.cb = T(1);
         A.cc = T(cc);
         A.filter = pending ? 1 : 0;
-        if (s->nbr || s->force_on) {
+        if (s->nbr) {
             A.collide_only = 1;
             const int rc = launch_stage<M_STAGE1>(s, A);
             A.collide_only = 0;
             if (rc) return rc;
-            if (s->force_on) {
-                if (int rc2 = force_collide(s, F0, A.dtau)) return rc2;
-            }
             return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
         }
         if (int rc = launch_stage<M_STAGE1>(s, A)) return rc;
@@ -456,6 +440,7 @@ struct Impl {
         GroupArgs<T> B = group_args(s);
         A.incr = 1;  // SSPRK weights sum to one
         B.incr = 1;
+        A.Fn = B.Fn = s->force_on ? static_cast<const T *>(s->Fn) : nullptr;
         T *F0 = st(s, 2), *FA = st(s, 3);
         bool pending = false;
         for (int64_t n = 0; n < nsteps; ++n) {
