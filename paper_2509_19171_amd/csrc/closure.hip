@@ -1,5 +1,5 @@
 // Learned relaxation-time closure: MLP inference (FP32 MFMA), training
-// kernels (forward, backward, deterministic weight-gradient sums, Adam),
+// kernels (loss and gradient in one pass, deterministic sums with Adam),
 // coarse graining of a fine simulation onto a coarse one of the same
 // elements, training targets, and their C entry points.
 //
@@ -63,14 +63,6 @@ __device__ __forceinline__ void stage_hidden(const float *__restrict__ P, float 
     }
 }
 
-// Work layout (floats): Xn[n][8], H1, H2, H3, D1, D2, D3 [n][64], Z[n], DZ[n],
-// grad[NTRAIN], loss partials [nblk] and the loss, weight-gradient partials
-// [nchunk][NTRAIN].
-struct TrainWork {
-    float *Xn, *H1, *H2, *H3, *D1, *D2, *D3, *Z, *DZ, *grad, *part, *wpart;
-};
-
-
 // ------------------------------------------------------------ inference --
 // One workgroup of 4 wavefronts; each wavefront runs a tile of RW = 32 rows
 // through 6 -> 64 -> 64 -> 64 -> 1 with v_mfma_f32_16x16x4f32 for the three
@@ -87,13 +79,8 @@ constexpr int RW = 32;  // rows per wavefront
 constexpr int64_t kInferMaxBlocks = 1024;
 constexpr int RT = RW / 16;
 
-// TRAIN: the forward pass of a training step on rows idx[s] of X (all rows
-// when idx is null): the normalised inputs, the three hidden layers and z of
-// sample s are stored in T for the back-propagation.
-template <bool TRAIN>
-__global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const float *__restrict__ X,
-                                             const int32_t *__restrict__ idx, int64_t n, float tau,
-                                             float *__restrict__ zout, float *__restrict__ dtau, TrainWork T)
+__global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const float *__restrict__ X, int64_t n,
+                                             float tau, float *__restrict__ zout, float *__restrict__ dtau)
 {
     __shared__ float sW1[NH][9];
     __shared__ float sW2[NH][NH + 1];
@@ -146,25 +133,13 @@ __global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const 
         {
             const int rr = l % RW, c0 = 4 * (l / RW);
             const int64_t r = base + w * RW + rr;
-            const int64_t row = (TRAIN && idx && r < n) ? (int64_t)idx[r] : r;
 #pragma unroll
             for (int c = c0; c < c0 + 4; ++c) {
-                const float x = (c < NF && r < n) ? (X[row * NF + c] - smean[c]) * sistd[c] : 0.f;
+                const float x = (c < NF && r < n) ? (X[r * NF + c] - smean[c]) * sistd[c] : 0.f;
                 sH[w][rr][c] = x;
-                if (TRAIN && r < n) T.Xn[r * 8 + c] = x;
             }
         }
         __builtin_amdgcn_wave_barrier();
-        // training: the hidden layer just written to sH, stored row by row
-        auto store_layer = [&](float *H) {
-            if constexpr (TRAIN) {
-                for (int q = l; q < RW * NH; q += 64) {
-                    const int rr = q / NH, c = q - rr * NH;
-                    const int64_t r = base + w * RW + rr;
-                    if (r < n) H[r * NH + c] = sH[w][rr][c];
-                }
-            }
-        };
         f4 acc[RT][4];
         // hidden layer 1 (K = 8)
 #pragma unroll
@@ -195,7 +170,6 @@ __global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const 
                     sH[w][16 * ti + 4 * lk + q][col] = tanh_fast(acc[ti][tj][q] + sb1[col]);
                 }
         __builtin_amdgcn_wave_barrier();
-        store_layer(T.H1);
         // hidden layers 2 and 3 (K = 64)
 #pragma unroll
         for (int layer = 0; layer < 2; ++layer) {
@@ -228,7 +202,6 @@ __global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const 
                         sH[w][16 * ti + 4 * lk + q][col] = tanh_fast(acc[ti][tj][q] + bl[col]);
                     }
             __builtin_amdgcn_wave_barrier();
-            store_layer(layer == 0 ? T.H2 : T.H3);
         }
         // output layer: two lanes per row, halves of the 64 products
         {
@@ -240,7 +213,6 @@ __global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const 
             z += b4;
             const int64_t r = base + w * RW + rr;
             if (h == 0 && r < n) {
-                if constexpr (TRAIN) T.Z[r] = z;
                 if (zout) zout[r] = z;
                 if (dtau) dtau[r] = guard_dtau(tau * softplusf(z), tau, dmax);
             }
@@ -250,284 +222,269 @@ __global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const 
 }
 
 // ------------------------------------------------------------- training --
-// backward workgroups: one tile of 4 RW rows each, at most 4096
+// Rows per tile and workgroups of the gradient kernel: one tile of 16 rows each
+// up to 256 workgroups (a minibatch of 4096 is one per CU), then several tiles
+// per workgroup, up to 1024 workgroups. The split depends on n alone.
+constexpr int TR = 16;
 constexpr int64_t train_blocks(int64_t n)
 {
-    return (n + 4 * RW - 1) / (4 * RW) < 4096 ? (n + 4 * RW - 1) / (4 * RW) : 4096;
+    const int64_t t = (n + TR - 1) / TR;
+    return t <= 256 ? t : t / 8 <= 256 ? 256 : t / 8 <= 1024 ? t / 8 : 1024;
 }
 
-// The weight gradient sums over the samples in chunks (at least 64 samples,
-// at most 1024 chunks), then over the chunks in order: the result does not
-// depend on the launch, and every chunk is a short loop of its own.
-constexpr int64_t wgrad_chunk(int64_t n) { return (n + 1023) / 1024 < 64 ? 64 : (n + 1023) / 1024; }
-constexpr int64_t wgrad_chunks(int64_t n) { return (n + wgrad_chunk(n) - 1) / wgrad_chunk(n); }
-// floats of training work memory for n rows (layout of carve_work)
-constexpr int64_t work_floats(int64_t n)
-{
-    return (8 + 6 * (int64_t)NH + 2) * n + NTRAIN + train_blocks(n) + 1 + wgrad_chunks(n) * NTRAIN;
-}
+// Work layout (floats): gradient [NTRAIN], loss partials [nblk] and the loss,
+// gradient partials [nblk][NTRAIN].
+struct TrainWork {
+    float *grad, *part, *wpart;
+};
+constexpr int64_t work_floats(int64_t n) { return NTRAIN + train_blocks(n) + 1 + train_blocks(n) * NTRAIN; }
 
 TrainWork carve_work(float *w, int64_t n)
 {
     TrainWork t;
-    t.Xn = w;
-    t.H1 = t.Xn + 8 * n;
-    t.H2 = t.H1 + NH * n;
-    t.H3 = t.H2 + NH * n;
-    t.D1 = t.H3 + NH * n;
-    t.D2 = t.D1 + NH * n;
-    t.D3 = t.D2 + NH * n;
-    t.Z = t.D3 + NH * n;
-    t.DZ = t.Z + n;
-    t.grad = t.DZ + n;
+    t.grad = w;
     t.part = t.grad + NTRAIN;
     t.wpart = t.part + train_blocks(n) + 1;
     return t;
 }
 
-// Back-propagation of the mean squared error of softplus(z) against y, on
-// the tiles of k_mlp (one tile of 4 RW rows per workgroup): the deltas of a
-// layer are formed in the wavefront's LDS buffer, D_l = (D_{l+1} W_{l+1}) (1 -
-// H_l^2) with v_mfma_f32_16x16x4f32 (A = deltas, B = W), and stored row by row.
-// dz = (2/n) (softplus(z) - y) sigmoid(z); D3 = dz w4 (1 - H3^2). Lane l holds
-// column l of the wavefront's activations, loaded before any delta is stored.
-// One loss partial (sum of squared residuals) per workgroup.
-__global__ void __launch_bounds__(256) k_train_bwd(const float *__restrict__ P, const float *__restrict__ y,
-                                                   const int32_t *__restrict__ idx, int64_t n, TrainWork T)
+// Loss and gradient of the mean squared error of softplus(z) against y: forward,
+// back-propagation and weight gradients of a tile of 16 rows in one pass, on
+// v_mfma_f32_16x16x4f32, partial sums of one workgroup at a time. Wavefront w
+// owns the hidden units 16 w .. 16 w + 15 of every layer:
+//   forward   H_l[s][16w + li] = tanh(sum_k H_{l-1}[s][k] W_l[16w + li][k] + b_l)
+//   backward  dz = (2/n) (softplus(z) - y) sigmoid(z), D3 = dz w4 (1 - H3^2),
+//             D_l[s][16w + li] = (sum_k D_{l+1}[s][k] W_{l+1}[k][16w + li]) (1 - H_l^2)
+//   gradient  G_l[16w + m][c] += sum_s D_l[s][16w + m] H_{l-1}[s][c]
+// so its weight fragments (64 registers, loaded once) and gradient tiles (36)
+// stay in registers over all its tiles; layers pass their activations and
+// deltas through LDS (6 barriers a tile). A result's lane holds the rows
+// 4 (l / 16) + q of its column; the sum over the samples takes them as its A
+// operand as they are (sample 4 (l / 16) + ks in step ks), without LDS. Bound by
+// latency: a minibatch of 4096 has one tile per CU. As five kernels (forward,
+// backward, weight gradient, sum, Adam) over activations in memory and tiles of
+// 128 rows on 32 CUs a step of 4096 rows took 57 us; with the sums and Adam in
+// one more kernel it takes 20 (14.5 + 5.4).
+__global__ void __launch_bounds__(256) k_train(const float *__restrict__ P, const float *__restrict__ X,
+                                               const float *__restrict__ y, const int32_t *__restrict__ idx,
+                                               int64_t n, float *__restrict__ part, float *__restrict__ wpart)
 {
-    __shared__ float sW2[NH][NH + 1];
-    __shared__ float sW3[NH][NH + 1];
-    __shared__ float sw4[NH];
-    __shared__ float sH[4][RW][NH + 1];
-    __shared__ float sdz[4][RW];
-    __shared__ float red[256];
-    const float *__restrict__ H1 = T.H1;
-    const float *__restrict__ H2 = T.H2;
-    const float *__restrict__ H3 = T.H3;
-    const float *__restrict__ Z = T.Z;
-    float *__restrict__ D1 = T.D1;
-    float *__restrict__ D2 = T.D2;
-    float *__restrict__ D3 = T.D3;
-    float *__restrict__ DZ = T.DZ;
-    const int tid = threadIdx.x;
-    {
-        const float w4 = tid < NH ? P[OFF_W4 + tid] : 0.f;
-        stage_hidden(P, sW2, sW3, tid);
-        if (tid < NH) sw4[tid] = w4;
+    constexpr int LD = 68;  // row stride: rows stay 16-byte aligned
+    __shared__ __attribute__((aligned(16))) float sH[3][TR][LD], sD[2][TR][LD];
+    __shared__ float sX[TR][17];
+    const int tid = threadIdx.x, w = tid / 64, l = tid % 64, li = l & 15, lk = l >> 4;
+    const int u = 16 * w + li;  // the lane's hidden unit
+    // weight fragments: step ks of a product over 64 units takes unit 16 lk + ks
+    float w1[2], wf[2][16], wb[2][16], w4k[16];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) w1[ks] = 4 * ks + lk < NF ? P[OFF_W1 + u * NF + 4 * ks + lk] : 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+        const int k = 16 * lk + ks;
+        wf[0][ks] = P[OFF_W2 + u * NH + k];
+        wf[1][ks] = P[OFF_W3 + u * NH + k];
+        wb[0][ks] = P[OFF_W3 + k * NH + u];
+        wb[1][ks] = P[OFF_W2 + k * NH + u];
+        w4k[ks] = P[OFF_W4 + k];
     }
-    __syncthreads();
-    const int w = tid / 64, l = tid % 64;
-    const int li = l & 15, lk = l >> 4;
-    const float two_n = 2.f / float(n);
-    float r2 = 0.f;
-    for (int64_t base = (int64_t)blockIdx.x * (4 * RW); base < n; base += (int64_t)gridDim.x * (4 * RW)) {
-        const int64_t r0 = base + w * RW;  // the wavefront's first row
-        float h1[RW], h2[RW], h3[RW];
+    const float bias[3] = {P[OFF_B1 + u], P[OFF_B2 + u], P[OFF_B3 + u]};
+    const float w4 = P[OFF_W4 + u], b4 = P[OFF_B4];
+    float mean[2], istd[2];
 #pragma unroll
-        for (int i = 0; i < RW; ++i) {
-            const bool ok = r0 + i < n;
-            h1[i] = ok ? H1[(r0 + i) * NH + l] : 0.f;
-            h2[i] = ok ? H2[(r0 + i) * NH + l] : 0.f;
-            h3[i] = ok ? H3[(r0 + i) * NH + l] : 0.f;
-        }
-        // residual and dz of the wavefront's rows
-        if (l < RW) {
-            const int64_t r = r0 + l;
-            float dz = 0.f;
-            if (r < n) {
-                const float z = Z[r];
-                const float res = softplusf(z) - y[idx ? (int64_t)idx[r] : r];
-                r2 += res * res;
-                dz = two_n * res / (1.f + expf(-z));
-                DZ[r] = dz;
-            }
-            sdz[w][l] = dz;
-        }
-        __builtin_amdgcn_wave_barrier();
-        // D3 = dz w4 (1 - H3^2)
-#pragma unroll
-        for (int i = 0; i < RW; ++i) {
-            const float d = sdz[w][i] * sw4[l] * (1.f - h3[i] * h3[i]);
-            if (r0 + i < n) D3[(r0 + i) * NH + l] = d;
-            sH[w][i][l] = d;
-        }
-        __builtin_amdgcn_wave_barrier();
-        // D2 from D3 through W3, then D1 from D2 through W2
-#pragma unroll
-        for (int layer = 0; layer < 2; ++layer) {
-            const float(*Wl)[NH + 1] = layer == 0 ? sW3 : sW2;
-            float *__restrict__ D = layer == 0 ? D2 : D1;
-            f4 acc[RT][4];
-#pragma unroll
-            for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
-            for (int ks = 0; ks < NH / 4; ++ks) {
-                float a[RT], b[4];
-#pragma unroll
-                for (int t = 0; t < RT; ++t) a[t] = sH[w][16 * t + li][4 * ks + lk];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) b[t] = Wl[4 * ks + lk][16 * t + li];
-#pragma unroll
-                for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < 4; ++tj)
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) sH[w][16 * ti + 4 * lk + q][16 * tj + li] = acc[ti][tj][q];
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int i = 0; i < RW; ++i) {
-                const float h = layer == 0 ? h2[i] : h1[i];
-                const float d = sH[w][i][l] * (1.f - h * h);
-                if (r0 + i < n) D[(r0 + i) * NH + l] = d;
-                sH[w][i][l] = d;
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
+    for (int ks = 0; ks < 2; ++ks) {
+        const int c = 4 * ks + lk;
+        mean[ks] = c < NF ? P[OFF_MEAN + c] : 0.f;
+        istd[ks] = c < NF ? 1.f / P[OFF_STD + c] : 0.f;
     }
-    red[tid] = r2;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (tid < k) red[tid] += red[tid + k];
-        __syncthreads();
-    }
-    if (tid == 0) T.part[blockIdx.x] = red[0];
-}
-
-// Partial gradients of one chunk of samples per workgroup. The weight blocks
-// G_l[m][k] = sum_s D_l[s][m] A_{l-1}[s][k] of W1 (inputs padded to 8
-// columns), W2 and W3 run on v_mfma_f32_16x16x4f32 with A = D^T and B =
-// A_{l-1}, wavefront w taking the output rows 16 w .. 16 w + 15; the biases,
-// w4 and b4 are plain sums in sample order.
-__global__ void __launch_bounds__(256) k_train_wgrad(int64_t n, int64_t chunk, TrainWork T)
-{
-    const int64_t s0 = (int64_t)blockIdx.x * chunk;
-    const int64_t s1 = s0 + chunk < n ? s0 + chunk : n;
-    const float *__restrict__ Xn = T.Xn;
-    const float *__restrict__ H1 = T.H1;
-    const float *__restrict__ H2 = T.H2;
-    const float *__restrict__ H3 = T.H3;
-    const float *__restrict__ D1 = T.D1;
-    const float *__restrict__ D2 = T.D2;
-    const float *__restrict__ D3 = T.D3;
-    const float *__restrict__ DZ = T.DZ;
-    float *__restrict__ out = T.wpart + (int64_t)blockIdx.x * NTRAIN;
-    const int tid = threadIdx.x, w = tid / 64, l = tid % 64;
-    const int li = l & 15, lk = l >> 4;
-    const int m = 16 * w + li;  // the output row this lane feeds as A
     f4 g1 = {0.f, 0.f, 0.f, 0.f}, g2[4], g3[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) g2[t] = g3[t] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t s = s0; s < s1; s += 4) {
-        const int64_t sr = s + lk;
-        const bool ok = sr < s1;
-        const float a1 = ok ? D1[sr * NH + m] : 0.f;
-        const float a2 = ok ? D2[sr * NH + m] : 0.f;
-        const float a3 = ok ? D3[sr * NH + m] : 0.f;
-        const float b1 = (ok && li < 8) ? Xn[sr * 8 + li] : 0.f;
-        float b2[4], b3[4];
+    float gb[3] = {0.f, 0.f, 0.f}, gw4 = 0.f, gb4 = 0.f, r2 = 0.f;
+    const float two_n = 2.f / float(n);
+    const int64_t tiles = (n + TR - 1) / TR;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        // the row of lane li, its inputs (columns lk and 4 + lk) and target
+        const int64_t r = tile * TR + li;
+        const bool ok = r < n;
+        const int64_t row = ok ? (idx ? (int64_t)idx[r] : r) : 0;
+        float a1[2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            b2[t] = ok ? H1[sr * NH + 16 * t + li] : 0.f;
-            b3[t] = ok ? H2[sr * NH + 16 * t + li] : 0.f;
+        for (int ks = 0; ks < 2; ++ks) {
+            const int c = 4 * ks + lk;
+            a1[ks] = (ok && c < NF) ? (X[row * NF + c] - mean[ks]) * istd[ks] : 0.f;
         }
-        g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, g1, 0, 0, 0);
+        const float yr = ok ? y[row] : 0.f;
+        float h[3][4];
+        f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            g2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2, b2[t], g2[t], 0, 0, 0);
-            g3[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a3, b3[t], g3[t], 0, 0, 0);
+        for (int ks = 0; ks < 2; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[ks], w1[ks], acc, 0, 0, 0);
+        if (w == 0) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) sX[li][4 * ks + lk] = a1[ks];
         }
-    }
-    // output (row 16 w + 4 lk + q, column 16 t + li) of each accumulator
+        // hidden layers: activations to LDS, then the next layer's product
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int row = 16 * w + 4 * lk + q;
-        if (li < NF) out[OFF_W1 - OFF_TRAIN + row * NF + li] = g1[q];
+        for (int layer = 0; layer < 3; ++layer) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            out[OFF_W2 - OFF_TRAIN + row * NH + 16 * t + li] = g2[t][q];
-            out[OFF_W3 - OFF_TRAIN + row * NH + 16 * t + li] = g3[t][q];
-        }
-    }
-    // b1, b2, b3 (one thread per entry), w4 (one per weight) and b4
-    {
-        const int k = tid % NH;
-        const float *__restrict__ D = tid < 64 ? D1 : tid < 128 ? D2 : D3;
-        float g = 0.f, gb = 0.f;
-        if (tid < 192) {
-#pragma unroll 16
-            for (int64_t s = s0; s < s1; ++s) g += D[s * NH + k];
-        } else {
-#pragma unroll 16
-            for (int64_t s = s0; s < s1; ++s) {
-                const float dz = DZ[s];
-                g += dz * H3[s * NH + k];
-                gb += dz;
+            for (int q = 0; q < 4; ++q) {
+                h[layer][q] = tanh_fast(acc[q] + bias[layer]);
+                sH[layer][4 * lk + q][u] = h[layer][q];
+            }
+            __syncthreads();
+            if (layer < 2) {
+                f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < 16; ks += 2) {
+                    c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sH[layer][li][16 * lk + ks], wf[layer][ks], c0, 0, 0, 0);
+                    c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sH[layer][li][16 * lk + ks + 1], wf[layer][ks + 1], c1, 0,
+                                                             0, 0);
+                }
+                acc = c0 + c1;
             }
         }
-        const int off = tid < 64 ? OFF_B1 : tid < 128 ? OFF_B2 : tid < 192 ? OFF_B3 : OFF_W4;
-        out[off - OFF_TRAIN + k] = g;
-        if (tid == 192) out[OFF_B4 - OFF_TRAIN] = gb;
+        // output, residual and dz of row li
+        float z = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) z += sH[2][li][16 * lk + ks] * w4k[ks];
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        z += b4;
+        const float res = ok ? softplusf(z) - yr : 0.f;
+        const float dz = two_n * res / (1.f + expf(-z));
+        if (l < 16) {
+            r2 += res * res;
+            gb4 += dz;
+        }
+        float d[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float dq = __shfl(dz, 4 * lk + q);
+            gw4 += dq * h[2][q];
+            d[q] = dq * w4 * (1.f - h[2][q] * h[2][q]);
+            sD[0][4 * lk + q][u] = d[q];
+            gb[2] += d[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int layer = 0; layer < 2; ++layer) {  // D2 from D3 through W3, then D1 from D2 through W2
+            f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 16; ks += 2) {
+                c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sD[layer][li][16 * lk + ks], wb[layer][ks], c0, 0, 0, 0);
+                c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sD[layer][li][16 * lk + ks + 1], wb[layer][ks + 1], c1, 0, 0,
+                                                         0);
+            }
+            // weight gradient of the layer above with its own deltas
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float b = sH[1 - layer][4 * lk + ks][16 * t + li];
+                    if (layer == 0) g3[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[ks], b, g3[t], 0, 0, 0);
+                    else g2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[ks], b, g2[t], 0, 0, 0);
+                }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float hq = h[1 - layer][q];
+                d[q] = (c0[q] + c1[q]) * (1.f - hq * hq);
+                if (layer == 0) sD[1][4 * lk + q][u] = d[q];
+                gb[1 - layer] += d[q];
+            }
+            if (layer == 0) __syncthreads();
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(d[ks], li < 8 ? sX[4 * lk + ks][li] : 0.f, g1, 0, 0, 0);
+        __syncthreads();  // the tile's LDS is free again
+    }
+    // gradient row 16 w + 4 lk + q, column 16 t + li of each tile
+    float *__restrict__ out = wpart + (int64_t)blockIdx.x * NTRAIN;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int m = 16 * w + 4 * lk + q;
+        if (li < NF) out[OFF_W1 - OFF_TRAIN + m * NF + li] = g1[q];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            out[OFF_W2 - OFF_TRAIN + m * NH + 16 * t + li] = g2[t][q];
+            out[OFF_W3 - OFF_TRAIN + m * NH + 16 * t + li] = g3[t][q];
+        }
+    }
+    // column sums over the four row quarters
+    float v[4] = {gb[0], gb[1], gb[2], gw4};
+    constexpr int off[4] = {OFF_B1, OFF_B2, OFF_B3, OFF_W4};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] += __shfl_xor(v[k], 16);
+        v[k] += __shfl_xor(v[k], 32);
+        if (l < 16) out[off[k] - OFF_TRAIN + u] = v[k];
+    }
+    if (w == 0) {
+#pragma unroll
+        for (int k = 8; k > 0; k >>= 1) {
+            r2 += __shfl_xor(r2, k);
+            gb4 += __shfl_xor(gb4, k);
+        }
+        if (l == 0) {
+            out[OFF_B4 - OFF_TRAIN] = gb4;
+            part[blockIdx.x] = r2;
+        }
     }
 }
 
-// the gradient: the partials summed in chunk order; the thread after the
-// last parameter sums the nb loss partials of the backward pass into *loss
-__global__ void __launch_bounds__(256) k_train_wsum(int64_t nchunk, int nb, int64_t n, TrainWork T, float *loss)
+// The partials summed (32 parameters per workgroup, eight runs of consecutive
+// partials each, the runs added in order: the result depends on n alone), then
+// with ADAM the update (Kingma & Ba, bias-corrected), else the gradient to grad.
+// The workgroup after the last parameter sums the loss partials into *loss.
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_train_sum(const float *__restrict__ wpart, const float *__restrict__ part,
+                                                   int nb, int64_t n, float *__restrict__ grad,
+                                                   float *__restrict__ loss, float *P, float *m, float *v, int64_t t,
+                                                   float lr, float b1, float b2, float eps)
 {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q == NTRAIN) {
-        const float *__restrict__ part = T.part;
-        float s = 0.f;
+    __shared__ float sh[8][32];
+    const int c = threadIdx.x % 32, seg = threadIdx.x / 32;
+    const int per = (nb + 7) / 8, k0 = seg * per, k1 = k0 + per < nb ? k0 + per : nb;
+    const bool is_loss = blockIdx.x == (NTRAIN + 31) / 32;
+    const int q = blockIdx.x * 32 + c;
+    float s = 0.f;
+    if (is_loss) {
+        for (int k = k0 + c; k < k1; k += 32) s += part[k];
+#pragma unroll
+        for (int k = 16; k > 0; k >>= 1) s += __shfl_xor(s, k, 32);
+    } else if (q < NTRAIN) {
 #pragma unroll 16
-        for (int b = 0; b < nb; ++b) s += part[b];
-        loss[0] = s / float(n);
+        for (int k = k0; k < k1; ++k) s += wpart[(int64_t)k * NTRAIN + q];
+    }
+    sh[seg][c] = s;
+    __syncthreads();
+    if (seg) return;
+    for (int k = 1; k < 8; ++k) s += sh[k][c];
+    if (is_loss) {
+        if (c == 0) loss[0] = s / float(n);
+        return;
     }
     if (q >= NTRAIN) return;
-    const float *__restrict__ wp = T.wpart;
-    float g = 0.f;
-#pragma unroll 16
-    for (int64_t c = 0; c < nchunk; ++c) g += wp[c * NTRAIN + q];
-    T.grad[q] = g;
+    if constexpr (ADAM) {
+        const float mq = b1 * m[q] + (1.f - b1) * s;
+        const float vq = b2 * v[q] + (1.f - b2) * s * s;
+        m[q] = mq;
+        v[q] = vq;
+        const float mh = mq / (1.f - powf(b1, float(t)));
+        const float vh = vq / (1.f - powf(b2, float(t)));
+        P[OFF_TRAIN + q] -= lr * mh / (sqrtf(vh) + eps);
+    } else {
+        grad[q] = s;
+    }
 }
 
-// forward, back-propagation, loss and gradient of n samples into T
+// gradient partials and loss partials of n samples into T
 void launch_gradient(const float *P, const float *X, const float *y, const int32_t *idx, int64_t n, TrainWork T,
-                     float *dloss, hipStream_t st)
+                     hipStream_t st)
 {
-    int64_t nbf = (n + 4 * RW - 1) / (4 * RW);
-    if (nbf > 4096) nbf = 4096;
-    hipLaunchKernelGGL(k_mlp<true>, dim3((unsigned)nbf), dim3(256), 0, st, P, X, idx, n, 1.f, nullptr, nullptr, T);
-    // one loss partial per backward workgroup
-    const int64_t nbb = train_blocks(n);
-    hipLaunchKernelGGL(k_train_bwd, dim3((unsigned)nbb), dim3(256), 0, st, P, y, idx, n, T);
-    const int64_t nchunk = wgrad_chunks(n);  // at most 1024
-    hipLaunchKernelGGL(k_train_wgrad, dim3((unsigned)nchunk), dim3(256), 0, st, n, wgrad_chunk(n), T);
-    hipLaunchKernelGGL(k_train_wsum, dim3((NTRAIN + 1 + 255) / 256), dim3(256), 0, st, nchunk, (int)nbb, n, T,
-                       dloss);
+    hipLaunchKernelGGL(k_train, dim3((unsigned)train_blocks(n)), dim3(256), 0, st, P, X, y, idx, n, T.part, T.wpart);
 }
 
-// Adam (Kingma & Ba), bias-corrected, on the trainable range
-__global__ void k_adam(float *P, float *m, float *v, const float *g, int64_t t, float lr, float b1, float b2, float eps)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= NTRAIN) return;
-    const float gq = g[q];
-    const float mq = b1 * m[q] + (1.f - b1) * gq;
-    const float vq = b2 * v[q] + (1.f - b2) * gq * gq;
-    m[q] = mq;
-    v[q] = vq;
-    const float mh = mq / (1.f - powf(b1, float(t)));
-    const float vh = vq / (1.f - powf(b2, float(t)));
-    P[OFF_TRAIN + q] -= lr * mh / (sqrtf(vh) + eps);
-}
+constexpr unsigned kSumBlocks = (NTRAIN + 31) / 32 + 1;
 
 // --------------------------------------------------------- coarse graining --
 // One workgroup per element, one thread per fine node; the projection matrix
@@ -768,8 +725,8 @@ int launch_mlp_infer(sel_sim *s)
     const int64_t n = s->Gtot;
     int64_t nb = (n + 4 * RW - 1) / (4 * RW);
     if (nb > kInferMaxBlocks) nb = kInferMaxBlocks;
-    hipLaunchKernelGGL(k_mlp<false>, dim3((unsigned)nb), dim3(256), 0, s->stream, s->cl_params, s->cl_X, nullptr, n,
-                       float(s->tau), nullptr, s->cl_dtau, TrainWork{});
+    hipLaunchKernelGGL(k_mlp, dim3((unsigned)nb), dim3(256), 0, s->stream, s->cl_params, s->cl_X, n, float(s->tau),
+                       nullptr, s->cl_dtau);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
         set_error(std::string("closure inference launch failed: ") + hipGetErrorString(err));
@@ -897,8 +854,8 @@ extern "C" int sel_mlp_forward(const float *d_params, const float *d_X, int64_t 
     if (n == 0) return SEL_OK;
     int64_t nb = (n + 4 * sel::RW - 1) / (4 * sel::RW);
     if (nb > sel::kInferMaxBlocks) nb = sel::kInferMaxBlocks;
-    hipLaunchKernelGGL(sel::k_mlp<false>, dim3((unsigned)nb), dim3(256), 0, static_cast<hipStream_t>(stream), d_params,
-                       d_X, nullptr, n, float(tau), d_z, d_dtau, sel::TrainWork{});
+    hipLaunchKernelGGL(sel::k_mlp, dim3((unsigned)nb), dim3(256), 0, static_cast<hipStream_t>(stream), d_params, d_X,
+                       n, float(tau), d_z, d_dtau);
     if (hipGetLastError() != hipSuccess) {
         set_error("sel_mlp_forward: launch failed");
         return SEL_EDEVICE;
@@ -916,9 +873,9 @@ static int train_step(const char *who, float *d_params, float *d_m, float *d_v, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     sel::TrainWork T = sel::carve_work(d_work, n);
     float *dloss = T.part + sel::train_blocks(n);
-    sel::launch_gradient(d_params, d_X, d_y, d_idx, n, T, dloss, st);
-    const unsigned gq = (sel::NTRAIN + 255) / 256;
-    hipLaunchKernelGGL(sel::k_adam, dim3(gq), dim3(256), 0, st, d_params, d_m, d_v, T.grad, t, float(lr), float(b1),
+    sel::launch_gradient(d_params, d_X, d_y, d_idx, n, T, st);
+    hipLaunchKernelGGL(sel::k_train_sum<true>, dim3(sel::kSumBlocks), dim3(256), 0, st, T.wpart, T.part,
+                       (int)sel::train_blocks(n), n, T.grad, dloss, d_params, d_m, d_v, t, float(lr), float(b1),
                        float(b2), float(eps));
     if (hipGetLastError() != hipSuccess) {
         set_error(std::string(who) + ": launch failed");
@@ -955,8 +912,8 @@ extern "C" int sel_mlp_train_step(float *d_params, float *d_m, float *d_v, const
 // host it only stands for the symbol): the device address is looked up once
 // per device with hipGetSymbolAddress, on the first call made with that
 // device current, and kept per device. Every call writes each value of the
-// work memory it later reads (forward activations, deltas, chunk partials,
-// gradient, loss), so nothing needs clearing between calls.
+// work memory it later reads (gradient partials, loss), so nothing needs clearing
+// between calls.
 constexpr int64_t kNoAllocRows = 4096;
 constexpr int64_t kNoAllocFloats = sel::work_floats(kNoAllocRows);
 static __device__ __align__(256) float scratch[kNoAllocFloats];
@@ -1015,7 +972,13 @@ extern "C" int sel_mlp_gradient(const float *d_params, const float *d_X, const f
     hipStream_t st = static_cast<hipStream_t>(stream);
     sel::TrainWork T = sel::carve_work(d_work, n);
     float *dloss = T.part + sel::train_blocks(n);
-    sel::launch_gradient(d_params, d_X, d_y, d_idx, n, T, dloss, st);
+    sel::launch_gradient(d_params, d_X, d_y, d_idx, n, T, st);
+    hipLaunchKernelGGL(sel::k_train_sum<false>, dim3(sel::kSumBlocks), dim3(256), 0, st, T.wpart, T.part,
+                       (int)sel::train_blocks(n), n, T.grad, dloss, nullptr, nullptr, nullptr, 0, 0.f, 0.f, 0.f, 0.f);
+    if (hipGetLastError() != hipSuccess) {
+        set_error("sel_mlp_gradient: launch failed");
+        return SEL_EDEVICE;
+    }
     if (hipMemcpyAsync(d_grad, T.grad, sizeof(float) * sel::NTRAIN, hipMemcpyDeviceToDevice, st) != hipSuccess) {
         set_error("sel_mlp_gradient: copy failed");
         return SEL_EDEVICE;
