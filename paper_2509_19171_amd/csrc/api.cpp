@@ -42,7 +42,7 @@ constexpr size_t kAlign = 256;
 struct Plan {
     size_t total = 0;
     size_t tabD, tabF, tabW, geoD, geoW, pcode, bpos, xyz, wJ, J, Gm, invw, invMb, bmap, bown, goff, gmem, ftag,
-        wallu, f[4], rtb, rhoc, Fn, io, red, flag, posmap, hidx, nbr = 0, tabL, aff = 0, cl_params = 0, cl_X = 0, cl_dtau = 0;
+        wallu, f[4], rtb, rhoc, Fn, io, red, flag, posmap, hidx, nbr = 0, tabL, aff = 0, nodes = 0, rtb2 = 0, rhoc2 = 0, cl_params = 0, cl_X = 0, cl_dtau = 0;
     int nred = 0;
     bool closure = false;
 };
@@ -137,6 +137,11 @@ Plan make_plan(const sel_mesh *m, const sel_params *p)
     if (m->dg) L.nbr = carve(c, 4 * m->nbr.size());
     L.hidx = carve(c, 4 * (size_t)(m->ngrp + 1));
     L.rhoc = carve(c, ts * (size_t)Gtot);
+    if (m->dim == 2 && !m->dg) {
+        L.nodes = carve(c, sizeof(int4) * (size_t)(E * np));
+        L.rtb2 = carve(c, ts * (size_t)p->Q * (size_t)m->plane);
+        L.rhoc2 = carve(c, ts * (size_t)Gtot);
+    }
     L.Fn = carve(c, ts * 3 * (size_t)Gtot);
     L.io = carve(c, 8 * (size_t)(E * np * (m->dim + 1)));
     int64_t nred = (E * np + 255) / 256;
@@ -377,6 +382,11 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     s->nmp = m->nmp;
     s->rhoc = b + L.rhoc;
     s->Fn = b + L.Fn;
+    if (m->dim == 2 && !m->dg) {
+        s->nodes = reinterpret_cast<int4 *>(b + L.nodes);
+        s->rtb2 = b + L.rtb2;
+        s->rhoc2 = b + L.rhoc2;
+    }
     s->io = reinterpret_cast<double *>(b + L.io);
     s->red = reinterpret_cast<double *>(b + L.red);
     s->nred = L.nred;
@@ -412,6 +422,25 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     UP(s->gmem, m->gmem.data(), 4 * m->gmem.size());
     UP(s->ftag, m->ftag.data(), 4 * m->ftag.size());
     UP(s->posmap, m->posmap.data(), 4 * m->posmap.size());
+    std::vector<int4> nodes;
+    if (s->nodes) {
+        // node table of the 2D stage kernels: interior slot or group, contribution
+        // slot, members of the group (0: interior) and owner, extra rank index
+        nodes.resize((size_t)nl);
+        for (int64_t e = 0; e < m->E; ++e)
+            for (int q = 0; q < m->np; ++q) {
+                const int pc = m->pcode[q];
+                if (pc >= 0) {
+                    nodes[e * m->np + q] = int4{pc, 0, 0, 0};
+                    continue;
+                }
+                const int64_t lb = e * m->nbe - pc - 1;
+                const int32_t g = m->bmap[lb];
+                nodes[e * m->np + q] = int4{g, m->posmap[lb], (m->goff[g + 1] - m->goff[g]) | (m->bown[lb] ? sel::kOwn : 0),
+                                            m->hidx[g] < 0 ? 0 : m->hidx[g]};
+            }
+        UP(s->nodes, nodes.data(), sizeof(int4) * nodes.size());
+    }
     if (m->dg) UP(s->nbr, m->nbr.data(), 4 * m->nbr.size());
     UP(s->hidx, m->hidx.data(), 4 * m->hidx.size());
     UP(s->io, rho, 8 * nl);

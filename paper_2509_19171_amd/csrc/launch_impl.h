@@ -1,7 +1,10 @@
 // Launch sequences of the SELBM kernels for one (dim, N, Q, storage) choice.
 #pragma once
 
+#include <utility>
+
 #include "kernels_big.h"
+#include "kernels_flat.h"
 #include "kernels_impl.h"
 #include "kernels_mfma.h"
 #include "kernels_relax.h"
@@ -431,9 +434,160 @@ struct Impl {
         return stage_pass(s, A, B, F0, FB, S, 3.0 / 8.0, 5.0 / 8.0, 0.25 * dt);
     }
 
+    // network increments of the closure for the current state (filtered first
+    // when `filter`): features, then inference
+    static int closure_increments(sel_sim *s, bool filter)
+    {
+        // the closure reads the filtered state: its features come from the
+        // filtered moment fields
+        hipEvent_t ev = nullptr;
+        if (int rc = tic(s, 4, ev)) return rc;
+        if (int rc = features(s, s->cl_X, 1, filter ? 1 : 0)) return rc;
+        if (int rc = toc(s, ev)) return rc;
+        if (int rc = tic(s, 5, ev)) return rc;
+        if (int rc = launch_mlp_infer(s)) return rc;
+        return toc(s, ev);
+    }
+
+    // 2D, continuous coupling: one kernel per stage (kernels_flat.h). Arrays: X
+    // the state, whose interior the first stage overwrites with its stage value
+    // and the last one with the result; Y the post-collision state; B = f[cur^1]
+    // the second stage value; Z the printed stages' third. A stage's boundary
+    // values are pending (in its contributions, to be combined from the two
+    // states f0 and fk) until the next kernel has assembled them, so no kernel
+    // may write the boundary part of those two: with SSPRK3, where Y is one of
+    // them, it alternates between f[2] and f[3].
+    static int step_flat(sel_sim *s, int64_t nsteps)
+    {
+        using FG = FlatGeo<N>;
+        const double dt = s->p.dt;
+        const bool filt = s->p.filter_type != SEL_FILTER_NONE, printed = s->p.rk == SEL_RK_PRINTED4;
+        GroupArgs<T> B = group_args(s);
+        FlatArgs<T> A{};
+        A.Gm = static_cast<const T *>(s->Gm);
+        A.invw = static_cast<const T *>(s->invw);
+        A.invMb = static_cast<const T *>(s->invMb);
+        A.D = static_cast<const T *>(s->tabD);
+        A.F = static_cast<const T *>(s->tabF);
+        A.wallu = static_cast<const T *>(s->wallu);
+        A.Fn = s->force_on ? static_cast<const T *>(s->Fn) : nullptr;
+        A.nodes = s->nodes;
+        A.ftag = s->ftag;
+        A.E = s->E;
+        A.Gi = s->Gi;
+        A.QGi = (int64_t)Q * s->Gi;
+        A.plane = s->plane;
+        A.ngp = s->ngp;
+        A.nmp = s->nmp;
+        A.dt = T(dt);
+        A.omega = T(s->omega);
+        A.tau = T(s->tau);
+        A.rho0 = T(s->p.rho0);
+        for (int q = 0; q < 2; ++q) A.g[q] = T(s->p.accel[q]);
+        for (int a = 0; a < Q; ++a) A.fsc[a] = T(s->fsc[a]);
+        B.Fn = A.Fn;
+        B.incr = 1;
+        T *rt[2] = {static_cast<T *>(s->rtb), static_cast<T *>(s->rtb2)};
+        T *rh[2] = {static_cast<T *>(s->rhoc), static_cast<T *>(s->rhoc2)};
+        int kt = 0, kr = 0;  // buffers of the last contributions and densities
+        T *X = st(s, s->cur), *W = st(s, s->cur ^ 1), *Y = st(s, 2), *Z = st(s, 3);
+        const dim3 grid((unsigned)xcd_grid((s->E + FG::EPB - 1) / FG::EPB)), block(FG::BLOCK);
+        auto launch = [&](auto MODE, int kind) -> int {
+            constexpr int mode = decltype(MODE)::value;
+            A.rin = rt[kt];
+            A.rout = rt[kt ^ 1];
+            A.rhop = A.rho = rh[kr];
+            A.rhoc = rh[kr ^ 1];
+            hipEvent_t ev = nullptr;
+            if (int rc = tic(s, kind, ev)) return rc;
+            hipLaunchKernelGGL((k_flat<N, T, DEV, mode>), grid, block, 0, s->stream, A);
+            SEL_LAUNCH_CHECK();
+            if (mode != F_FILTER) kt ^= 1;
+            if (mode == F_FIRST) kr ^= 1;
+            return toc(s, ev);
+        };
+        // what the boundary nodes of the last result are combined from
+        auto pending = [&](const T *f0, const T *fk, double ca, double cb, double cc) {
+            A.pf0 = f0;
+            A.pfk = fk;
+            A.pca = T(ca);
+            A.pcb = T(cb);
+            A.pcc = T(cc);
+            A.pend = 1;
+        };
+        auto assemble = [&]() -> int {
+            B.rtb = rt[kt];
+            B.rhoc = rh[kr];
+            B.f0 = A.pf0;
+            B.fk = A.pfk;
+            B.out = X;
+            B.ca = A.pca;
+            B.cb = A.pcb;
+            B.cc = A.pcc;
+            A.pend = 0;
+            return launch_group(s, B);
+        };
+        // out = ca f0 + cb fk + cc L(fk), fk pending from before
+        auto stage = [&](T *fk, const T *f0, T *out, double ca, double cb, double cc) -> int {
+            A.op = A.opb = fk;
+            A.f0in = f0;
+            A.out = out;
+            A.ca = T(ca);
+            A.cb = T(cb);
+            A.cc = T(cc);
+            if (int rc = launch(std::integral_constant<int, F_STAGE>{}, 1)) return rc;
+            pending(f0, fk, ca, cb, cc);
+            return SEL_OK;
+        };
+        A.filter = 0;
+        for (int64_t n = 0; n < nsteps; ++n) {
+            A.dtau = nullptr;
+            if (s->closure_on) {
+                // the features read the state: it is assembled first
+                if (A.pend)
+                    if (int rc = assemble()) return rc;
+                if (int rc = closure_increments(s, A.filter != 0)) return rc;
+                A.dtau = s->cl_dtau;
+            }
+            if (!printed && A.pend) std::swap(Y, Z);
+            const double c1 = printed ? dt / 3.0 : dt;
+            A.op = X;
+            A.out = X;
+            A.y = Y;
+            A.ca = T(0);
+            A.cb = T(1);
+            A.cc = T(c1);
+            if (int rc = launch(std::integral_constant<int, F_FIRST>{}, 0)) return rc;
+            pending(Y, Y, 0.0, 1.0, c1);
+            if (printed) {
+                if (int rc = stage(X, Y, W, 9.0 / 4.0, -5.0 / 4.0, 0.75 * dt)) return rc;
+                if (int rc = stage(W, X, Z, 8.0 / 9.0, 1.0 / 9.0, 2.0 / 3.0 * dt)) return rc;
+                if (int rc = stage(Z, W, X, 3.0 / 8.0, 5.0 / 8.0, 0.25 * dt)) return rc;
+            } else {
+                if (int rc = stage(X, Y, W, 0.75, 0.25, 0.25 * dt)) return rc;
+                if (int rc = stage(W, Y, X, 1.0 / 3.0, 2.0 / 3.0, 2.0 / 3.0 * dt)) return rc;
+            }
+            A.filter = filt ? 1 : 0;
+            s->time += dt;
+            s->nstep += 1;
+        }
+        if (!filt) return assemble();
+        // into the array that is neither read here nor the state
+        T *O = printed ? Y : Z;
+        A.op = X;
+        A.out = O;
+        if (int rc = launch(std::integral_constant<int, F_FILTER>{}, 3)) return rc;
+        std::swap(s->f[s->cur ^ 1], s->f[O == st(s, 2) ? 2 : 3]);
+        s->cur ^= 1;
+        return SEL_OK;
+    }
+
     static int step(sel_sim *s, int64_t nsteps)
     {
         if (nsteps <= 0) return SEL_OK;
+        if constexpr (DIM == 2) {
+            if (!s->nbr) return step_flat(s, nsteps);
+        }
         const double dt = s->p.dt;
         const bool filt = s->p.filter_type != SEL_FILTER_NONE;
         StageArgs<T> A = stage_args(s);
@@ -445,17 +599,7 @@ struct Impl {
         bool pending = false;
         for (int64_t n = 0; n < nsteps; ++n) {
             if (s->closure_on) {
-                // the closure reads the filtered state: its features come from
-                // the filtered moment fields (the filter itself stays fused
-                // into the first stage); then the network infers the
-                // per-node relaxation-time increments
-                hipEvent_t ev = nullptr;
-                if (int rc = tic(s, 4, ev)) return rc;
-                if (int rc = features(s, s->cl_X, 1, pending ? 1 : 0)) return rc;
-                if (int rc = toc(s, ev)) return rc;
-                if (int rc = tic(s, 5, ev)) return rc;
-                if (int rc = launch_mlp_infer(s)) return rc;
-                if (int rc = toc(s, ev)) return rc;
+                if (int rc = closure_increments(s, pending)) return rc;
                 A.dtau = s->cl_dtau;
             } else {
                 A.dtau = nullptr;

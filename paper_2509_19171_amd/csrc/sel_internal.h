@@ -13,6 +13,7 @@ namespace sel {
 
 constexpr int kMaxN1 = 16;  // host tables up to N = 15
 constexpr int kMaxQ = 27;
+constexpr int kOwn = 1 << 30;  // node table: the node's first copy (kernels_flat.h)
 constexpr int kLineTab = 2 * (2 * (kMaxN1 / 2 + 1) * (kMaxN1 / 2));  // values of the two mirrored line tables at most
 
 // Host-side tables of the spectral element (built in tables.cpp).
@@ -124,6 +125,9 @@ struct sel_sim {
     void *f[4] = {};           // T [nstate]: state, f0, stage a, stage b
     void *rtb = nullptr;       // T [Q][plane] element contributions of boundary nodes
     void *rhoc = nullptr;      // T [Gtot]
+    // 2D, continuous coupling (kernels_flat.h): node table and second buffers
+    int4 *nodes = nullptr;     // [E][np]
+    void *rtb2 = nullptr, *rhoc2 = nullptr;
     double *io = nullptr;      // FP64 [E][np][dim+1] (moments / per-velocity transfers)
     double *red = nullptr;     // FP64 [nred][8] partial sums
     int nred = 0;
