@@ -115,8 +115,12 @@ __global__ void __launch_bounds__((FlatGeo<N>::BLOCK)) k_flat(FlatArgs<T> A)
         static_for<0, Q>([&](auto AA) {
             constexpr int a = decltype(AA)::value;
             v[a] = A.op[si.base + a * si.stride];
-            if constexpr (MODE == F_STAGE) f0[a] = inner ? A.f0in[si.base + a * si.stride] : T(0);
         });
+        if (MODE == F_STAGE && inner)
+            static_for<0, Q>([&](auto AA) {
+                constexpr int a = decltype(AA)::value;
+                f0[MODE == F_STAGE ? a : 0] = A.f0in[si.base + a * si.stride];
+            });
         if (inner && MODE != F_FILTER) {
             invw = A.invw[gix];
             if constexpr (MODE == F_STAGE) rho = A.rho[gix];
@@ -124,24 +128,28 @@ __global__ void __launch_bounds__((FlatGeo<N>::BLOCK)) k_flat(FlatArgs<T> A)
     } else if (valid) {
         // the node's members in ascending order, then the update of the last stage
         const T *r = A.rin + nd.x, *x = A.rin + 2 * A.ngp + nd.w;
+        // (all loads first; a member's block is skipped where no node has it)
         T s[Q] = {}, s1[Q] = {}, s2[Q] = {}, s3[Q] = {}, b0[Q], bk[Q];
         static_for<0, Q>([&](auto AA) {
             constexpr int a = decltype(AA)::value;
+            if constexpr (a > 0) s[a] = r[a * A.plane];
             b0[a] = A.pf0[si.base + a * si.stride];
             bk[a] = A.pfk[si.base + a * si.stride];
-            if constexpr (a > 0) {
-                s[a] = r[a * A.plane];
-                if (nm > 1) s1[a] = r[a * A.plane + A.ngp];
-                if (nm > 2) s2[a] = x[a * A.plane];
-                if (nm > 3) s3[a] = x[a * A.plane + A.nmp];
-            }
         });
         const T iM = A.invMb[nd.x], rg = A.rhop[gix];
+        auto member = [&](bool has, const T *q, T (&d)[Q]) {
+            if (has)
+                static_for<1, Q>([&](auto AA) {
+                    constexpr int a = decltype(AA)::value;
+                    d[a] = q[a * A.plane];
+                });
+        };
+        member(nm > 1, r + A.ngp, s1);
+        member(nm > 2, x, s2);
+        member(nm > 3, x + A.nmp, s3);
         static_for<1, Q>([&](auto AA) {
             constexpr int a = decltype(AA)::value;
-            if (nm > 1) s[a] += s1[a];
-            if (nm > 2) s[a] += s2[a];
-            if (nm > 3) s[a] += s3[a];
+            s[a] = ((s[a] + s1[a]) + s2[a]) + s3[a];
         });
         for (int t = 4; t < nm; ++t)
             static_for<1, Q>([&](auto AA) {
