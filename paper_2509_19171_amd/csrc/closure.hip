@@ -42,182 +42,101 @@ __device__ __forceinline__ float guard_dtau(float d, float tau, float dmax)
     return (d == d && d >= 0.f && d <= dmax * tau) ? d : 0.f;
 }
 
-// W2 and W3 into LDS by a workgroup of 256 threads: every load of a thread is
-// issued before its first LDS store, so the workgroup waits for one memory
-// round trip instead of one per loop iteration.
-__device__ __forceinline__ void stage_hidden(const float *__restrict__ P, float (*sW2)[NH + 1],
-                                             float (*sW3)[NH + 1], int tid)
-{
-    constexpr int PER = NH * NH / 256;
-    float a[PER], b[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        a[i] = P[OFF_W2 + tid + 256 * i];
-        b[i] = P[OFF_W3 + tid + 256 * i];
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int q = tid + 256 * i;
-        sW2[q / NH][q % NH] = a[i];
-        sW3[q / NH][q % NH] = b[i];
-    }
-}
-
 // ------------------------------------------------------------ inference --
-// One workgroup of 4 wavefronts; each wavefront runs a tile of RW = 32 rows
-// through 6 -> 64 -> 64 -> 64 -> 1 with v_mfma_f32_16x16x4f32 for the three
-// hidden layers (A = activations, B = W^T, 2 x 4 output tiles of 16 x 16,
-// activations re-laid out through LDS between layers). 71 KB of LDS, so two
-// workgroups share a CU. Each wavefront's activation buffer is its own and a
-// wavefront's LDS operations complete in order, so inside the row loop only
-// compiler scheduling barriers separate the layers: the four wavefronts of a
-// workgroup run independently.
-constexpr int RW = 32;  // rows per wavefront
-// inference grid: at most 1024 workgroups (four per CU, two resident at a
-// time), each looping over its tiles, so that a workgroup stages the weights
-// for many tiles (4096 workgroups took 1.3% longer on 1.4 M rows)
-constexpr int64_t kInferMaxBlocks = 1024;
+// Tiles of RW = 32 rows through 6 -> 64 -> 64 -> 64 -> 1, a workgroup of 4
+// wavefronts per tile, with v_mfma_f32_16x16x4f32 for the three hidden layers.
+// Wavefront w owns the hidden units 16 w .. 16 w + 15: its weight fragments stay
+// in 34 registers over all tiles, and only the activations pass through LDS
+// (two buffers of 8.5 KB, one barrier per layer), so that five workgroups share a
+// CU and the tanh of some runs under the matrix products of others. Bound by
+// the matrix units (14.5 us for 131 k rows) and the tanh (9 us), which overlap
+// little, and the last of 4 rounds of tiles: 131 k rows 36.5 -> 34.6 us, 14 k rows
+// 10.7 -> 8.8, against weights in LDS (71 KB, two workgroups per CU). Tiles of 16
+// rows 39, of 64 rows 36.8.
+constexpr int RW = 32;  // rows per tile
 constexpr int RT = RW / 16;
+// five resident workgroups per CU, each looping over its tiles
+constexpr int64_t kInferMaxBlocks = 5 * 256;
 
-__global__ void __launch_bounds__(256) k_mlp(const float *__restrict__ P, const float *__restrict__ X, int64_t n,
-                                             float tau, float *__restrict__ zout, float *__restrict__ dtau)
+__global__ void __launch_bounds__(256, 5) k_mlp(const float *__restrict__ P, const float *__restrict__ X, int64_t n,
+                                                float tau, float *__restrict__ zout, float *__restrict__ dtau)
 {
-    __shared__ float sW1[NH][9];
-    __shared__ float sW2[NH][NH + 1];
-    __shared__ float sW3[NH][NH + 1];
-    __shared__ float sb1[NH], sb2[NH], sb3[NH], sw4[NH];
-    __shared__ float sH[4][RW][NH + 1];
-    __shared__ float smean[NF], sistd[NF];
-    const int tid = threadIdx.x;
-    const float b4 = P[OFF_B4], dmax = P[OFF_DMAX];
-    {
-        // all loads first (one round trip), then the LDS stores
-        float w1v[2], bv[4] = {0.f, 0.f, 0.f, 0.f}, mv = 0.f, sv = 1.f;
+    constexpr int LD = 68;  // row stride: rows stay 16-byte aligned
+    constexpr int RPW = RW / 4;  // output rows per wavefront
+    __shared__ __attribute__((aligned(16))) float sH[2][RW][LD];
+    __shared__ float sz[2][RW];
+    const int tid = threadIdx.x, w = tid / 64, l = tid % 64, li = l & 15, lk = l >> 4;
+    const int u = 16 * w + li;  // the lane's hidden unit
+    // weight fragments: step ks of a product over 64 units takes unit 16 lk + ks
+    float w1[2], wf[2][16], mean[2], istd[2], w4[RPW];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int q = tid + 256 * i, r = q / 8, c = q % 8;
-            w1v[i] = (c < NF) ? P[OFF_W1 + r * NF + c] : 0.f;
-        }
-        if (tid < NH) {
-            bv[0] = P[OFF_B1 + tid];
-            bv[1] = P[OFF_B2 + tid];
-            bv[2] = P[OFF_B3 + tid];
-            bv[3] = P[OFF_W4 + tid];
-        }
-        if (tid < NF) {
-            mv = P[OFF_MEAN + tid];
-            sv = P[OFF_STD + tid];
-        }
-        stage_hidden(P, sW2, sW3, tid);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int q = tid + 256 * i;
-            sW1[q / 8][q % 8] = w1v[i];
-        }
-        if (tid < NH) {
-            sb1[tid] = bv[0];
-            sb2[tid] = bv[1];
-            sb3[tid] = bv[2];
-            sw4[tid] = bv[3];
-        }
-        if (tid < NF) {
-            smean[tid] = mv;
-            sistd[tid] = 1.f / sv;
-        }
+    for (int ks = 0; ks < 2; ++ks) {
+        const int c = 4 * ks + lk;
+        w1[ks] = c < NF ? P[OFF_W1 + u * NF + c] : 0.f;
+        mean[ks] = c < NF ? P[OFF_MEAN + c] : 0.f;
+        istd[ks] = c < NF ? 1.f / P[OFF_STD + c] : 0.f;
     }
-    __syncthreads();
-    const int w = tid / 64, l = tid % 64;
-    const int li = l & 15, lk = l >> 4;
-    for (int64_t base = (int64_t)blockIdx.x * (4 * RW); base < n; base += (int64_t)gridDim.x * (4 * RW)) {
-        // normalised inputs, K padded to 8: lane l fills row l % RW, columns 4 (l / RW) .. +3
-        {
-            const int rr = l % RW, c0 = 4 * (l / RW);
-            const int64_t r = base + w * RW + rr;
 #pragma unroll
-            for (int c = c0; c < c0 + 4; ++c) {
-                const float x = (c < NF && r < n) ? (X[r * NF + c] - smean[c]) * sistd[c] : 0.f;
-                sH[w][rr][c] = x;
+    for (int ks = 0; ks < 16; ++ks) {
+        wf[0][ks] = P[OFF_W2 + u * NH + 16 * lk + ks];
+        wf[1][ks] = P[OFF_W3 + u * NH + 16 * lk + ks];
+    }
+    // output layer: row RPW w + l % RPW of the tile, units RPW (l / RPW) .. + RPW - 1
+#pragma unroll
+    for (int c = 0; c < RPW; ++c) w4[c] = P[OFF_W4 + RPW * (l / RPW) + c];
+    const float bias[3] = {P[OFF_B1 + u], P[OFF_B2 + u], P[OFF_B3 + u]};
+    const float b4 = P[OFF_B4], dmax = P[OFF_DMAX];
+    const int64_t tiles = (n + RW - 1) / RW;
+    int turn = 0;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x, ++turn) {
+        f4 acc[RT];
+        // normalised inputs (columns 6 and 7 zero), hidden layer 1
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int64_t r = tile * RW + 16 * t + li;
+            acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const int c = 4 * ks + lk;
+                const float x = (c < NF && r < n) ? (X[r * NF + c] - mean[ks]) * istd[ks] : 0.f;
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, w1[ks], acc[t], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        f4 acc[RT][4];
-        // hidden layer 1 (K = 8)
 #pragma unroll
-        for (int ti = 0; ti < RT; ++ti)
+        for (int layer = 0; layer < 3; ++layer) {
+            float(*H)[LD] = sH[layer & 1];
 #pragma unroll
-            for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            float a[RT], b[4];
+                for (int q = 0; q < 4; ++q) H[16 * t + 4 * lk + q][u] = tanh_fast(acc[t][q] + bias[layer]);
+            __syncthreads();
+            if (layer < 2) {
 #pragma unroll
-            for (int t = 0; t < RT; ++t) a[t] = sH[w][16 * t + li][4 * ks + lk];
+                for (int t = 0; t < RT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < 4; ++t) b[t] = sW1[16 * t + li][4 * ks + lk];
+                for (int ks = 0; ks < 16; ++ks)
 #pragma unroll
-            for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 4; ++tj)
-                    acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-            for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = 16 * tj + li;
-                    sH[w][16 * ti + 4 * lk + q][col] = tanh_fast(acc[ti][tj][q] + sb1[col]);
-                }
-        __builtin_amdgcn_wave_barrier();
-        // hidden layers 2 and 3 (K = 64)
-#pragma unroll
-        for (int layer = 0; layer < 2; ++layer) {
-            const float(*Wl)[NH + 1] = layer == 0 ? sW2 : sW3;
-            const float *bl = layer == 0 ? sb2 : sb3;
-#pragma unroll
-            for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
-            for (int ks = 0; ks < NH / 4; ++ks) {
-                float a[RT], b[4];
-#pragma unroll
-                for (int t = 0; t < RT; ++t) a[t] = sH[w][16 * t + li][4 * ks + lk];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) b[t] = Wl[16 * t + li][4 * ks + lk];
-#pragma unroll
-                for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < 4; ++tj)
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int ti = 0; ti < RT; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int col = 16 * tj + li;
-                        sH[w][16 * ti + 4 * lk + q][col] = tanh_fast(acc[ti][tj][q] + bl[col]);
-                    }
-            __builtin_amdgcn_wave_barrier();
-        }
-        // output layer: two lanes per row, halves of the 64 products
-        {
-            const int rr = l % RW, h = l / RW;
-            float z = 0.f;
-#pragma unroll 8
-            for (int c = 32 * h; c < 32 * h + 32; ++c) z += sH[w][rr][c] * sw4[c];
-            z += __shfl_xor(z, 32);
-            z += b4;
-            const int64_t r = base + w * RW + rr;
-            if (h == 0 && r < n) {
-                if (zout) zout[r] = z;
-                if (dtau) dtau[r] = guard_dtau(tau * softplusf(z), tau, dmax);
+                    for (int t = 0; t < RT; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(H[16 * t + li][16 * lk + ks], wf[layer][ks],
+                                                                     acc[t], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        const int rr = RPW * w + l % RPW;
+        float z = 0.f;
+#pragma unroll
+        for (int c = 0; c < RPW; ++c) z += sH[0][rr][RPW * (l / RPW) + c] * w4[c];
+#pragma unroll
+        for (int k = RPW; k < 64; k *= 2) z += __shfl_xor(z, k);
+        if (l < RPW) sz[turn & 1][rr] = z + b4;
+        __syncthreads();  // layer 3 read before the next tile's layer 1 is written
+        // softplus and guard for the whole tile by one wavefront, in turn (by
+        // each of them for its own rows they were a third of the arithmetic)
+        const int64_t r = tile * RW + l;
+        if (w == (turn & 3) && l < RW && r < n) {
+            const float zr = sz[turn & 1][l];
+            if (zout) zout[r] = zr;
+            if (dtau) dtau[r] = guard_dtau(tau * softplusf(zr), tau, dmax);
+        }
     }
 }
 
@@ -723,7 +642,7 @@ int check_pair(const sel_sim *f, const sel_sim *c)
 int launch_mlp_infer(sel_sim *s)
 {
     const int64_t n = s->Gtot;
-    int64_t nb = (n + 4 * RW - 1) / (4 * RW);
+    int64_t nb = (n + RW - 1) / RW;
     if (nb > kInferMaxBlocks) nb = kInferMaxBlocks;
     hipLaunchKernelGGL(k_mlp, dim3((unsigned)nb), dim3(256), 0, s->stream, s->cl_params, s->cl_X, n, float(s->tau),
                        nullptr, s->cl_dtau);
@@ -852,7 +771,7 @@ extern "C" int sel_mlp_forward(const float *d_params, const float *d_X, int64_t 
         return SEL_EINVAL;
     }
     if (n == 0) return SEL_OK;
-    int64_t nb = (n + 4 * sel::RW - 1) / (4 * sel::RW);
+    int64_t nb = (n + sel::RW - 1) / sel::RW;
     if (nb > sel::kInferMaxBlocks) nb = sel::kInferMaxBlocks;
     hipLaunchKernelGGL(sel::k_mlp, dim3((unsigned)nb), dim3(256), 0, static_cast<hipStream_t>(stream), d_params, d_X,
                        n, float(tau), d_z, d_dtau);
