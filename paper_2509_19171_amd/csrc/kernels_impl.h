@@ -353,6 +353,8 @@ __device__ __forceinline__ void interface_flux(T &rt, T v, const T (&Gr)[DIM][DI
 }
 
 // ----------------------------------------------------------- stage kernel --
+// M_STAGE1 (filter and collision) and M_FILTER serve 2D alone, with M_STAGE23
+// for the discontinuous coupling; 3D takes M_STAGE23 for curved elements.
 enum { M_STAGE1 = 0, M_STAGE23 = 1, M_LOCAL = 2, M_FILTER = 3 };
 
 template <typename T>
@@ -381,18 +383,17 @@ struct StageArgs {
     const float *dtau;    // learned-closure increments per node id (nullptr: plain method)
     const int32_t *nbr;   // discontinuous coupling: [E][2 dim][(N+1)^(dim-1)] group across each face (nullptr: continuous)
     const T *Fn;          // force density per node id [Gtot][3], added to rho g (nullptr: none)
-    int collide_only;     // M_STAGE1: stop after writing the post-collision state
 };
 
 // DGC: the discontinuous coupling's interface flux is compiled in (a
 // separate instantiation, so the continuous kernels carry none of it).
 template <int DIM, int N, int Q, typename T, bool DEV, int MODE, bool DGC = false>
-__global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || MODE == M_STAGE1) && sizeof(T) == 4) ? 4 : 1)) k_stage(StageArgs<T> A)
+__global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && sizeof(T) == 4) ? 4 : 1)) k_stage(StageArgs<T> A)
 {
     using GG = Geo<DIM, N>;
     constexpr int n1 = GG::n1, NP = GG::NP, NI = GG::NI, NB = GG::NB, EPB = GG::EPB;
-    // first stage and filter keep all velocities of the node in registers
-    // (collision and filter need them); later stages stream the velocities
+    // collision and filter keep all velocities of the node in registers; the
+    // stages stream the velocities
     // with a software prefetch one chunk ahead. Velocities are processed in
     // chunks of NA planes per LDS barrier.
     constexpr bool ALLQ = (MODE == M_STAGE1 || MODE == M_FILTER);
@@ -407,23 +408,13 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     // of the node are loaded at once (every load in flight together), all Q
     // planes of the element go to LDS behind one barrier, and the velocities
     // are then processed without further waits on global memory
-    constexpr bool FULL = DIF && EPB == 1 && MODE != M_FILTER && Q * NP * 4 <= 80 * 1024;
-    // FP32 filter with all Q planes in LDS (first stage and filter-only
-    // launch); FP64 uses it for the filter-only launch (110 KB of LDS at
-    // N = 7, Q = 27: one workgroup per CU, which costs the stages more than
-    // the chunked passes)
-    constexpr bool FF = EPB == 1 && ALLQ && (DIF ? Q * NP * 4 <= 80 * 1024 : (MODE == M_FILTER && Q * NP * 8 <= 120 * 1024));
+    constexpr bool FULL = DIF && EPB == 1 && !ALLQ && Q * NP * 4 <= 80 * 1024;
     // later stages also stage their results through LDS for coalesced stores
-    constexpr bool STG = FULL && (MODE == M_STAGE23 || MODE == M_STAGE1);
-    constexpr int PL_N = (ALLQ ? 3 : 2) * NA * EPB * NP;
-    constexpr int LDS_N = (FULL || FF) ? (ALLQ ? (Q * NP > PL_N ? Q * NP : PL_N) : Q * NP) : PL_N;
+    constexpr bool STG = FULL && MODE == M_STAGE23;
+    constexpr int LDS_N = FULL ? Q * NP : 2 * NA * EPB * NP;
     __shared__ __attribute__((aligned(16))) T lds[LDS_N];
     T(*pl)[EPB * NP] = reinterpret_cast<T(*)[EPB * NP]>(lds);
     __shared__ T sF[ALLQ ? n1 * n1 : 1];
-    // FP32 first stage: D-hat in LDS as well (its rows are read after the
-    // collision, where global loads would add a memory latency)
-    constexpr bool SD = MODE == M_STAGE1 && FULL;
-    __shared__ T sD[SD ? n1 * n1 : 1];
 
     const int tid = threadIdx.x;
     const int le = tid / NP;
@@ -436,10 +427,6 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     if constexpr (ALLQ) {
         if (filt)
             for (int q = tid; q < n1 * n1; q += GG::BLOCK) sF[q] = A.F[q];
-    }
-    if constexpr (SD) {
-        for (int q = tid; q < n1 * n1; q += GG::BLOCK) sD[q] = A.D[q];
-        if (!filt) __syncthreads();  // else the filter's first barrier makes it visible
     }
     const int i = p % n1;
     const int j = (p / n1) % n1;
@@ -496,11 +483,10 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
             });
         }
     };
-    // first stage with the filter, and the later stages (FP32, one element
-    // per workgroup): the element's values go straight to the planes, one slot
-    // per thread (interior slots contiguous per velocity, boundary slots
-    // through their node group)
-    constexpr bool SLOT = FULL && EPB == 1 && NB + NI == NP && ((MODE == M_STAGE1 && FF) || MODE == M_STAGE23);
+    // later stages (FP32, one element per workgroup): the element's values go
+    // straight to the planes, one slot per thread (interior slots contiguous per
+    // velocity, boundary slots through their node group)
+    constexpr bool SLOT = FULL && NB + NI == NP && MODE == M_STAGE23;
     bool slotted = false;
     // the node's metric terms and inverse mass: with the slot loads they are
     // issued together with the element's values and parked in LDS (18 KB at
@@ -512,7 +498,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     bool have_metric = false;
     __shared__ T sG[SLOT ? (DIM * DIM + 1) * NP : 1];
     if constexpr (SLOT) {
-        if (MODE == M_STAGE23 || filt) {
+        {
             slotted = true;
             const T *src;
             int node, stride;
@@ -565,56 +551,12 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     }
 
     if constexpr (ALLQ) {
-        if (filt && FF) {
-            // explicit modal filter (Sec. 2.2.3), all velocities per pass: the
-            // node's values go to the Q planes, each pass is computed into
-            // registers and written back (two barriers per pass)
-            if (!slotted) {
-                static_for<0, Q>([&](auto AA) {
-                    constexpr int a = decltype(AA)::value;
-                    pl[a][p] = fq[a];
-                });
-            }
-            __syncthreads();  // planes and sF visible
-            if (slotted) {
-                static_for<0, Q>([&](auto AA) {
-                    constexpr int a = decltype(AA)::value;
-                    fq[a] = pl[a][p];
-                });
-            }
-            static_for<0, DIM>([&](auto MM) {
-                constexpr int m = decltype(MM)::value;
-                const int row = (m == 0) ? rowr : (m == 1) ? rows : rowt;
-                constexpr int st = (m == 0) ? 1 : (m == 1) ? n1 : n1 * n1;
-                const int ir = (m == 0) ? i : (m == 1) ? j : k;
-                // rows 0 and N of F are unit vectors: nodes at the ends of
-                // the line keep their value (exactly); along t in 3D at N = 7
-                // these are whole wavefronts (k is uniform)
-                if (!(m == DIM - 1 && (ir == 0 || ir == N))) {
-                    static_for<0, Q>([&](auto AA) {
-                        constexpr int a = decltype(AA)::value;
-                        const T x = fq[a];
-                        T t = 0;
-#pragma unroll
-                        for (int q = 0; q < n1; ++q) t += sF[ir * n1 + q] * (pl[a][row + st * q] - x);
-                        fq[a] = t + x;
-                    });
-                }
-                if constexpr (m + 1 < DIM) {
-                    __syncthreads();  // every read of this pass done
-                    static_for<0, Q>([&](auto AA) {
-                        constexpr int a = decltype(AA)::value;
-                        pl[a][p] = fq[a];
-                    });
-                    __syncthreads();
-                }
-            });
-        } else if (filt) {
+        if (filt) {
             __syncthreads();  // sF visible
             // explicit modal filter (Sec. 2.2.3): (F x F x F) applied one direction at a time
             static_for<0, NC>([&](auto CC) {
                 constexpr int c = decltype(CC)::value;
-                T t1v[NA], t2v[NA];
+                T t1v[NA];
                 static_for<0, NA>([&](auto UU) {
                     constexpr int u = decltype(UU)::value, a = c * NA + u;
                     if constexpr (a < Q) pl[u][base + p] = fq[a];
@@ -647,28 +589,9 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
                             else t2 += sF[j * n1 + q] * pl[NA + u][rows + n1 * q];
                         }
                         if constexpr (DIF) t2 += x;
-                        t2v[u] = t2;
-                        if constexpr (DIM == 3) pl[2 * NA + u][base + p] = t2;
-                        else fq[a] = t2;
+                        fq[a] = t2;
                     }
                 });
-                if constexpr (DIM == 3) {
-                    __syncthreads();
-                    static_for<0, NA>([&](auto UU) {
-                        constexpr int u = decltype(UU)::value, a = c * NA + u;
-                        if constexpr (a < Q) {
-                            const T x = t2v[u];
-                            T t3 = 0;
-#pragma unroll
-                            for (int q = 0; q < n1; ++q) {
-                                if constexpr (DIF) t3 += sF[k * n1 + q] * (pl[2 * NA + u][rowt + n1 * n1 * q] - x);
-                                else t3 += sF[k * n1 + q] * pl[2 * NA + u][rowt + n1 * n1 * q];
-                            }
-                            if constexpr (DIF) t3 += x;
-                            fq[a] = t3;
-                        }
-                    });
-                }
             });
         }
         if constexpr (MODE == M_FILTER) {
@@ -701,7 +624,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
                 A.rhoc[gix] = rho;
             }
         }
-        if (A.collide_only) return;  // whole workgroup
+        return;
     } else if constexpr (MODE == M_STAGE23) {
         if (valid && inner) rho = A.rhoc[gix];
     }
@@ -710,7 +633,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
     T Di[n1], Dj[n1], Dk[n1];
 #pragma unroll
     for (int c = 0; c < n1; ++c) {
-        const T *Dt = SD ? sD : A.D;
+        const T *Dt = A.D;
         Di[c] = Dt[i * n1 + c];
         Dj[c] = Dt[j * n1 + c];
         Dk[c] = (DIM == 3) ? Dt[k * n1 + c] : T(0);
@@ -817,7 +740,6 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
             });
         } else {
             // the filter passes of the first stage used the same LDS
-            if constexpr (ALLQ) __syncthreads();
             static_for<0, Q>([&](auto AA) {
                 constexpr int a = decltype(AA)::value;
                 pl[a][p] = fq[a];

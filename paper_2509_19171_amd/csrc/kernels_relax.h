@@ -293,6 +293,61 @@ __global__ void __launch_bounds__((FilterGeo<N, Q, T>::BLOCK)) k_filter(RelaxArg
     }
 }
 
+// Moments of 3D meshes at every element node, FP64 (Eqs. pressure, momentum).
+// The populations are read in slot order, as runs, and the results go through
+// LDS to be written as runs in node order (one thread per node in node order
+// read six slots to a run and wrote 24-byte pieces: 16^3 elements N = 7 FP32 78
+// us, here 59; D3Q19 N = 8 89 and 69; 12^3 N = 7 FP64 41 and 33.5).
+template <int N>
+struct MomentGeo {
+    static constexpr int NP = (N + 1) * (N + 1) * (N + 1), EPB = NP >= 256 ? 1 : 256 / NP;
+};
+template <int N, int Q, typename T, bool DEV>
+__global__ void __launch_bounds__(256) k_moments_el(const T *f, const int32_t *bpos, const int32_t *bmap, int64_t E,
+                                                    int64_t QGi, double rho0, double *rho, double *u)
+{
+    using SG = StreamGeo<N, Q, T>;
+    constexpr int n1 = SG::n1, NP = SG::NP, NI = SG::NI, NB = SG::NB, M1 = N - 1, EPB = MomentGeo<N>::EPB;
+    __shared__ double sm[4][EPB * NP];
+    const int64_t nblk = (E + EPB - 1) / EPB, eb = xcd_block(nblk);
+    if (eb >= nblk) return;  // whole workgroup
+    const int64_t left = E - eb * EPB;
+    const uint32_t nodes = (left < EPB ? (int)left : EPB) * NP;
+    for (uint32_t q = threadIdx.x; q < nodes; q += 256) {
+        const uint32_t le = q / NP, s = q % NP;
+        const int64_t e = eb * EPB + le;
+        uint32_t p, st;
+        int64_t base;
+        if (s < NI) {
+            p = (s % M1 + 1) + n1 * (s / M1 % M1 + 1) + n1 * n1 * (s / (M1 * M1) + 1);
+            base = e * (int64_t)(Q * NI) + s;
+            st = NI;
+        } else {
+            p = bpos[s - NI];
+            base = QGi + tile_at<Q>(bmap[e * NB + s - NI]);
+            st = kTile;
+        }
+        double m = 0, j[3] = {0, 0, 0};
+        static_for<0, Q>([&](auto AA) {
+            constexpr int a = decltype(AA)::value;
+            const double v = double(f[base + a * st]);
+            m += v;
+            if constexpr (lat_e<3, Q>(a, 0) != 0) j[0] += lat_e<3, Q>(a, 0) * v;
+            if constexpr (lat_e<3, Q>(a, 1) != 0) j[1] += lat_e<3, Q>(a, 1) * v;
+            if constexpr (lat_e<3, Q>(a, 2) != 0) j[2] += lat_e<3, Q>(a, 2) * v;
+        });
+        const double r = DEV ? rho0 + m : m;
+        p += le * NP;
+        sm[0][p] = r;
+        double *su = &sm[1][0] + 3 * p;
+        for (int c = 0; c < 3; ++c) su[c] = j[c] / r;
+    }
+    __syncthreads();
+    const int64_t o = eb * EPB * NP;
+    for (uint32_t q = threadIdx.x; q < nodes; q += 256) rho[o + q] = sm[0][q];
+    for (uint32_t q = threadIdx.x; q < 3 * nodes; q += 256) u[3 * o + q] = (&sm[1][0])[q];
+}
+
 // The collision alone, one thread per node id. op and out may be the same.
 template <int N, int Q, typename T, bool DEV>
 __global__ void __launch_bounds__(256) k_collide(RelaxArgs<T> A)

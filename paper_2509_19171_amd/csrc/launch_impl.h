@@ -273,16 +273,12 @@ struct Impl {
         // the discontinuous coupling adds its interface flux here
         // wavefronts per 64 groups: four fill the chip sooner on small meshes
         // (D3Q27 FP32, us with 2 and 4: 8^3 elements N = 3 10.8 and 7.9, 1024
-        // elements N = 5 13.9 and 10.6, 16^3 N = 7 55 and 53.5); two where the
-        // memory is the limit and a thread's values are few loads anyway: FP64
-        // (12^3 N = 7 46.4 and 47.4) and the discontinuous coupling, which looks
-        // up its faces per thread (10^3 N = 5 15.6 and 17.8)
-        const bool two = B.nbr || (sizeof(T) == 8 && s->ngrp > (1 << 17));
-        const dim3 grid((unsigned)xcd_grid((s->ngrp * (two ? 2 : 4) + 255) / 256));
+        // elements N = 5 13.9 and 10.6, 16^3 N = 7 55 and 53.5) and cost nothing on
+        // large ones; two with the discontinuous coupling, which looks up its
+        // faces per thread (10^3 N = 5 15.6 and 17.8)
+        const dim3 grid((unsigned)xcd_grid((s->ngrp * (B.nbr ? 2 : 4) + 255) / 256));
         if (B.nbr) {
             hipLaunchKernelGGL((k_group_split<Q, T, 2, N>), grid, block, 0, s->stream, B);
-        } else if (two) {
-            hipLaunchKernelGGL((k_group_split<Q, T, 2>), grid, block, 0, s->stream, B);
         } else {
             hipLaunchKernelGGL((k_group_split<Q, T, 4>), grid, block, 0, s->stream, B);
         }
@@ -374,11 +370,8 @@ struct Impl {
     }
 
     // First stage: filter (when pending) and collide the state S into the
-    // post-collision state y = F0, then FA = y + cc L(y). 3D: the relaxation,
-    // then a streaming pass like the later stages'. 2D: the continuous coupling
-    // streams in the same kernel (a shared node's post-collision value is the
-    // same in every element); the discontinuous coupling needs the
-    // post-collision values across faces and streams in a second pass.
+    // post-collision state y = F0, then FA = y + cc L(y) by a streaming pass like
+    // the later stages'. (2D: the discontinuous coupling alone.)
     static int stage_one(sel_sim *s, StageArgs<T> &A, GroupArgs<T> &B, const T *S, T *F0, T *FA, double cc,
                          bool pending)
     {
@@ -386,28 +379,11 @@ struct Impl {
             if (int rc = launch_relax(s, S, F0, pending, true, A.dtau, s->force_on)) return rc;
             return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
         } else {
-        A.op = S;
-        A.f0out = F0;
-        A.out = FA;
-        A.ca = T(0);
-        A.cb = T(1);
-        A.cc = T(cc);
-        A.filter = pending ? 1 : 0;
-        if (s->nbr) {
-            A.collide_only = 1;
-            const int rc = launch_stage<M_STAGE1>(s, A);
-            A.collide_only = 0;
-            if (rc) return rc;
+            A.op = S;
+            A.f0out = F0;
+            A.filter = pending ? 1 : 0;
+            if (int rc = launch_stage<M_STAGE1>(s, A)) return rc;
             return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
-        }
-        if (int rc = launch_stage<M_STAGE1>(s, A)) return rc;
-        B.f0 = F0;
-        B.fk = F0;
-        B.out = FA;
-        B.ca = T(0);
-        B.cb = T(1);
-        B.cc = T(cc);
-        return launch_group(s, B);
         }
     }
 
@@ -637,9 +613,15 @@ struct Impl {
 
     static int moments(sel_sim *s, double *d_rho, double *d_u)
     {
-        const int64_t nl = s->E * NP;
-        hipLaunchKernelGGL((k_moments<DIM, Q, T, DEV>), dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s->stream,
-                           nodemap(s), st(s, s->cur), s->p.rho0, d_rho, d_u);
+        if constexpr (DIM == 3) {
+            constexpr int EPM = MomentGeo<N>::EPB;
+            hipLaunchKernelGGL((k_moments_el<N, Q, T, DEV>), dim3((unsigned)xcd_grid((s->E + EPM - 1) / EPM)), dim3(256), 0,
+                               s->stream, st(s, s->cur), s->bpos, s->bmap, s->E, (int64_t)Q * s->Gi, s->p.rho0, d_rho, d_u);
+        } else {
+            const int64_t nl = s->E * NP;
+            hipLaunchKernelGGL((k_moments<DIM, Q, T, DEV>), dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s->stream,
+                               nodemap(s), st(s, s->cur), s->p.rho0, d_rho, d_u);
+        }
         SEL_LAUNCH_CHECK();
         return SEL_OK;
     }
