@@ -62,7 +62,7 @@ def method_bytes(dim, Q, s):
     return {"stage1": s * (2 + geo), "later_stage": s * (3 + geo), "step": s * (8 + 3 * geo)}
 
 
-def algorithmic_bytes(info, Q, s, affine=False):
+def algorithmic_bytes(info, Q, s):
     """Per step: the method's bytes (method_bytes) times the node-velocities.
     Per launch, this implementation's own count of what each kernel must move
     at least, every value once:
@@ -73,8 +73,7 @@ def algorithmic_bytes(info, Q, s, affine=False):
       stage23  read the operand at every unique node, read the post-collision
                state and write the result at interior nodes, write the
                boundary-node contributions, read the metric, the interior
-               inverse mass and density (none of the three on a 3D mesh of
-               affine elements, ``affine``);
+               inverse mass and density;
       assembly read the contributions, read two states and write one at every
                node group, read the group mass and density and the member
                lists (4-byte ints);
@@ -88,7 +87,7 @@ def algorithmic_bytes(info, Q, s, affine=False):
     step = method_bytes(dim, Q, s)["step"] * nv
     per = {
         "stage1": s * (2 * Q * G + G + (Q * E * npn + E * npn * dim * dim if dim == 2 else 0)),
-        "stage23": s * (Q * G + 2 * Q * E * ni + Q * E * nb + (0 if affine else E * npn * dim * dim + 2 * E * ni)),
+        "stage23": s * (Q * G + 2 * Q * E * ni + Q * E * nb + E * npn * dim * dim + 2 * E * ni),
         "assembly": s * (Q * E * nb + 3 * Q * ng + 2 * ng) + 4 * (E * nb + ng),
         "filter": s * 2 * Q * G,
         # closure: read the state at every unique node and the metric, write 6 features per node id
@@ -243,7 +242,7 @@ def time_config(name, case, precision, steps, warmup, torch, closure=None, hbm=T
     f = time_form(case, precision, steps, warmup, torch, closure=closure)
     info = f["info"]
     s = 4 if precision.startswith("fp32") else 8
-    nv, step_bytes, per = algorithmic_bytes(info, case.Q, s, affine=True)
+    nv, step_bytes, per = algorithmic_bytes(info, case.Q, s)
     if closure is not None:
         step_bytes += per["features"] + per["network"]
     out = {"workload": name, "precision": precision + ("+closure" if closure is not None else ""),
@@ -345,7 +344,13 @@ def main():
                           "GBs_read_plus_write": 2 * nbytes / (ms * 1e-3) / 1e9}), flush=True)
         return
     sel.load()
-    case = I.case_tgv3d(nel=args.nel, N=args.order, Q=args.q, steps=0)
+    box = I.case_tgv3d(nel=args.nel, N=args.order, Q=args.q, steps=0)
+    # the workload is specified on the general per-node metric: one interior
+    # node is moved by 1e-9 of the smallest spacing, so that the library does not
+    # take the box for a mesh of affine elements (timed beside it, below)
+    case = dataclasses.replace(box, mesh=dataclasses.replace(box.mesh, xyz=box.mesh.xyz.copy()))
+    n1 = args.order + 1
+    case.mesh.xyz[0, 1 + n1 + n1 * n1, 0] += 1e-9 * I.min_node_spacing(box.mesh)
     # the closure and the discontinuous coupling take one thread per element
     # node: not built for elements of more than 1024 nodes
     one_thread_per_node = (args.order + 1) ** 3 <= 1024
@@ -356,6 +361,10 @@ def main():
         w = args.warmup if prec == args.precision else max(5, args.warmup // 2)
         print(f"[bench] timing {prec}: {w} warmup + {k} steps", file=sys.stderr, flush=True)
         forms[prec] = time_form(case, prec, k, w, torch)
+    affine = None
+    if not args.no_other_form:
+        print("[bench] timing the affine elements' path", file=sys.stderr, flush=True)
+        affine = time_form(box, args.precision, max(20, args.steps // 2), max(5, args.warmup // 2), torch)
     if not args.no_other_form and one_thread_per_node:
         # closure form: same workload, features and network inferred every step
         # (a seeded untrained network; the cost does not depend on the weights)
@@ -373,7 +382,7 @@ def main():
     head = forms[args.precision]
     info = head["info"]
     s = 4 if args.precision == "fp32dev" else 8
-    nv, step_bytes, per_kind = algorithmic_bytes(info, case.Q, s, affine=True)
+    nv, step_bytes, per_kind = algorithmic_bytes(info, case.Q, s)
     value = nv / (head["ms_per_step"] * 1e-3) / 1e9
     kern = head["kernels"]
     avg = {k: v[0] / v[1] for k, v in kern.items() if v[1]}
@@ -438,6 +447,9 @@ def main():
         "src_hash": src_hash(),
     }
     if not args.no_other_form:
+        # the same box without the moved node: elements found affine, no metric per node
+        result["affine_elements"] = {"value": round(nv / (affine["ms_per_step"] * 1e-3) / 1e9, 3), "unit": "GNVU/s",
+                                     "ms_per_step": round(affine["ms_per_step"], 5)}
         if one_thread_per_node:
             result["closure_training"] = training
         print("[bench] timing the other workload shapes", file=sys.stderr, flush=True)

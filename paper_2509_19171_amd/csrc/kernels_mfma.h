@@ -91,6 +91,7 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
 
     // ------------------------------------------------------------ loads --
     mf4 fkv[3], f0v[3];
+    const bool same = A.f0in == A.op;  // first stage: the operand is the post-collision state, read once
     {
         const mf4 *op4 = reinterpret_cast<const mf4 *>(A.op + ib);
         const mf4 *z4 = reinterpret_cast<const mf4 *>(A.f0in + ib);
@@ -100,7 +101,7 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
             const bool ok = q < NQ4;
             fkv[r] = ok ? op4[q] : mf4{0.f, 0.f, 0.f, 0.f};
             // read once per stage: non-temporal, like the metric
-            f0v[r] = ok ? __builtin_nontemporal_load(z4 + q) : mf4{0.f, 0.f, 0.f, 0.f};
+            f0v[r] = (ok && !same) ? __builtin_nontemporal_load(z4 + q) : mf4{0.f, 0.f, 0.f, 0.f};
         }
     }
     // boundary slots one per thread (threads 0 .. NB-1): the slot's group is
@@ -275,7 +276,7 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
                     L[3] += e0 * x[1] + e1 * x[2] + e2 * x[3];
                 }
                 const mf4 fk = fkv[r];
-                const mf4 f0 = f0v[r];
+                const mf4 f0 = same ? fk : f0v[r];
                 mf4 o;
                 if (A.incr) {
                     o = fk + (A.ca * (f0 - fk) + A.cc * L);
