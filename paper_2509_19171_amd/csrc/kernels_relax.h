@@ -72,6 +72,7 @@ struct RelaxArgs {
     const uint8_t *bown;
     int64_t E, Gi, Gtot, QGi;
     T dt, omega, tau, rho0, g[3];
+    int split;  // k_filter: workgroups an element's velocities are dealt to
 };
 
 // collision of one node with its body force, force per node and closure increment
@@ -207,8 +208,10 @@ __global__ void __launch_bounds__((FilterGeo<N, Q, T>::BLOCK)) k_filter(RelaxArg
     constexpr int NIR = (NI + NL - 1) / NL, NBR = SG::NBR;
     __shared__ T lds[G::UPB][PL];
     const uint32_t tid = threadIdx.x;
-    const int64_t e = xcd_block(A.E);
-    if (e >= A.E) return;  // whole workgroup
+    const int64_t wg = xcd_block(A.E * A.split);
+    if (wg >= A.E * A.split) return;  // whole workgroup
+    const int64_t e = A.split == 1 ? wg : wg / A.split;
+    const uint32_t part = (uint32_t)(wg - e * A.split);
     uint32_t unit, line;
     bool act;
     if constexpr (G::WAVE) {
@@ -247,7 +250,7 @@ __global__ void __launch_bounds__((FilterGeo<N, Q, T>::BLOCK)) k_filter(RelaxArg
     }
     T *P = lds[unit];
     const uint32_t i = line % n1, j = line / n1;
-    for (uint32_t a0 = 0; a0 < Q; a0 += G::UPB) {
+    for (uint32_t a0 = part * G::UPB; a0 < Q; a0 += A.split * G::UPB) {
         const uint32_t a = a0 + unit;
         const bool on = act && a < Q;
         const T *q = A.op + e * (int64_t)(Q * NI) + (on ? a : 0) * (uint32_t)NI;

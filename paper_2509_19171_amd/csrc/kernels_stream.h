@@ -178,6 +178,7 @@ struct StreamArgs {
     int incr;       // ca + cb = 1: increment form (rk_combine)
     int body;       // some pf is not zero
     int same;       // f0in is op: read once
+    int split;      // workgroups an element's pairs are dealt to
     T w[N + 1];     // GLL weights
     int32_t pa[NPAIR], pb[NPAIR];  // velocities of each pair, e_pb = -e_pa
     T pe[NPAIR][3], pt[NPAIR], pf[NPAIR];  // e, weight and F* per unit density of pa
@@ -195,8 +196,10 @@ __global__ void __launch_bounds__((StreamGeo<N, Q, T>::BLOCK), (sizeof(T) == 4 &
     __shared__ T lds[SG::UPB][3][PL];
 
     const uint32_t tid = threadIdx.x;
-    const int64_t e = xcd_block(A.E);
-    if (e >= A.E) return;  // whole workgroup
+    const int64_t wg = xcd_block(A.E * A.split);
+    if (wg >= A.E * A.split) return;  // whole workgroup
+    const int64_t e = A.split == 1 ? wg : wg / A.split;
+    const uint32_t part = (uint32_t)(wg - e * A.split);
     uint32_t unit, line;
     bool act;
     if constexpr (SG::WAVE) {
@@ -226,7 +229,7 @@ __global__ void __launch_bounds__((StreamGeo<N, Q, T>::BLOCK), (sizeof(T) == 4 &
     const ConstPtr<T> ga = (ConstPtr<T>)(A.aff + e * 10);
 
     // the rest velocity neither streams nor meets a wall
-    for (uint32_t s = tid; s < NI; s += SG::BLOCK) {
+    for (uint32_t s = part ? NI : tid; s < NI; s += SG::BLOCK) {
         const T v = A.op[ib + s];
         A.out[ib + s] = rk_combine(A.ca, A.cb, A.cc, A.f0in[ib + s], v, T(0), A.incr);
     }
@@ -409,7 +412,7 @@ __global__ void __launch_bounds__((StreamGeo<N, Q, T>::BLOCK), (sizeof(T) == 4 &
 
     // the next velocity's values are loaded while one is streamed
     auto pair_of = [&](uint32_t it, bool &on) {
-        const uint32_t pr = it * SG::UPB + unit;
+        const uint32_t pr = (it * A.split + part) * SG::UPB + unit;
         on = act && pr < NPAIR;
         return on ? pr : 0u;
     };
@@ -417,9 +420,9 @@ __global__ void __launch_bounds__((StreamGeo<N, Q, T>::BLOCK), (sizeof(T) == 4 &
     bool on;
     uint32_t pi = pair_of(0, on);
     if (on) load(va, A.pa[pi]);
-    for (uint32_t it = 0; it < SG::PASSES; ++it) {
+    for (uint32_t it = 0; (it * A.split + part) * SG::UPB < NPAIR; ++it) {
         if constexpr (SG::WAVE) {
-            if (__builtin_amdgcn_readfirstlane(it * SG::UPB + unit) >= NPAIR) break;
+            if (__builtin_amdgcn_readfirstlane((it * A.split + part) * SG::UPB + unit) >= NPAIR) break;
         }
         if (on) load(vb, A.pb[pi]);
         velocity(std::integral_constant<int, 0>{}, pi, on, va);

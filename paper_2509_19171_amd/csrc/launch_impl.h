@@ -121,6 +121,18 @@ struct Impl {
         return hipEventRecord(b, s->stream) == hipSuccess ? SEL_OK : SEL_EDEVICE;
     }
 
+    // Workgroups an element's passes over its velocities are dealt to: small
+    // meshes leave most of the chip idle while one workgroup goes through an
+    // element's passes in turn: about four workgroups per CU, two of those with
+    // more than 40 KB of LDS (Taylor-Green N = 7 FP64, three steps: 4^3 elements
+    // 352 -> 290 us, 6^3 403 -> 340; 8^3 N = 12, two per CU already, stays unsplit:
+    // 121 us a stage against 132)
+    static int split_of(int64_t E, int passes, size_t lds)
+    {
+        const int64_t n = (lds > 40 * 1024 ? 512 : 1024) / E;
+        return n <= 1 ? 1 : n < passes ? (int)n : passes;
+    }
+
     // affine elements (3D): one streaming pass (kernels_stream.h) with the operands of A
     static int launch_stream(sel_sim *s, const StageArgs<T> &A)
     {
@@ -163,7 +175,8 @@ struct Impl {
         }
         hipEvent_t ev = nullptr;
         if (int rc = tic(s, 1, ev)) return rc;
-        const dim3 grid((unsigned)xcd_grid(A.E)), block(SG::BLOCK);
+        S.split = split_of(A.E, SG::PASSES, sizeof(T) * SG::UPB * 3 * SG::PL);
+        const dim3 grid((unsigned)xcd_grid(A.E * S.split)), block(SG::BLOCK);
         if (s->nwall > 0) {
             hipLaunchKernelGGL((k_stream<N, Q, T, true>), grid, block, 0, s->stream, S);
         } else {
@@ -209,8 +222,10 @@ struct Impl {
         } else {
             if constexpr (!RG::FUSED) {
                 if (filter) {
-                    hipLaunchKernelGGL((k_filter<N, Q, T>), dim3((unsigned)xcd_grid(s->E)),
-                                       dim3(FilterGeo<N, Q, T>::BLOCK), 0, s->stream, A);
+                    using FG = FilterGeo<N, Q, T>;
+                    A.split = split_of(s->E, (Q + FG::UPB - 1) / FG::UPB, sizeof(T) * FG::UPB * StreamGeo<N, Q, T>::PL);
+                    hipLaunchKernelGGL((k_filter<N, Q, T>), dim3((unsigned)xcd_grid(s->E * A.split)),
+                                       dim3(FG::BLOCK), 0, s->stream, A);
                     A.op = A.out;
                 }
             }
@@ -274,10 +289,12 @@ struct Impl {
         // wavefronts per 64 groups: four fill the chip sooner on small meshes
         // (D3Q27 FP32, us with 2 and 4: 8^3 elements N = 3 10.8 and 7.9, 1024
         // elements N = 5 13.9 and 10.6, 16^3 N = 7 55 and 53.5) and cost nothing on
-        // large ones; two with the discontinuous coupling, which looks up its
-        // faces per thread (10^3 N = 5 15.6 and 17.8)
-        const dim3 grid((unsigned)xcd_grid((s->ngrp * (B.nbr ? 2 : 4) + 255) / 256));
-        if (B.nbr) {
+        // large ones; two on large meshes with the discontinuous coupling, which
+        // looks up its faces per thread (10^3 N = 5, 152 k groups, 15.6 and 17.8)
+        const dim3 grid((unsigned)xcd_grid((s->ngrp * (B.nbr && s->ngrp > (1 << 16) ? 2 : 4) + 255) / 256));
+        if (B.nbr && s->ngrp <= (1 << 16)) {
+            hipLaunchKernelGGL((k_group_split<Q, T, 4, N>), grid, block, 0, s->stream, B);
+        } else if (B.nbr) {
             hipLaunchKernelGGL((k_group_split<Q, T, 2, N>), grid, block, 0, s->stream, B);
         } else {
             hipLaunchKernelGGL((k_group_split<Q, T, 4>), grid, block, 0, s->stream, B);
