@@ -38,7 +38,7 @@ template <typename T>
 struct FlatArgs {
     const T *op;          // operand: interior nodes, and boundary nodes when nothing is pending
     const T *f0in;        // stage: post-collision state (interior)
-    T *out;               // result: interior nodes (filter: all)
+    T *out;               // result: interior nodes (filter: all; may be op, with an assembly pending)
     T *y;                 // first stage: post-collision state
     T *opb;               // stage: the operand's boundary nodes are stored here
     // pending assembly of the operand's boundary nodes: pca f0 + pcb fk + pcc L

@@ -565,14 +565,12 @@ struct Impl {
             s->nstep += 1;
         }
         if (!filt) return assemble();
-        // into the array that is neither read here nor the state
-        T *O = printed ? Y : Z;
-        A.op = X;
-        A.out = O;
-        if (int rc = launch(std::integral_constant<int, F_FILTER>{}, 3)) return rc;
-        std::swap(s->f[s->cur ^ 1], s->f[O == st(s, 2) ? 2 : 3]);
-        s->cur ^= 1;
-        return SEL_OK;
+        // in place: a node's interior value is read by its own thread alone, and its
+        // boundary value comes from the two states it is pending on, neither of
+        // them X. The state keeps its array from call to call, so a captured call
+        // (or a sequence of them) replays from its own result.
+        A.op = A.out = X;
+        return launch(std::integral_constant<int, F_FILTER>{}, 3);
     }
 
     static int step(sel_sim *s, int64_t nsteps)
