@@ -223,16 +223,18 @@ __global__ void __launch_bounds__(256) k_train(const float *__restrict__ P, cons
     const int64_t tiles = (n + TR - 1) / TR;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         // the row of lane li, its inputs (columns lk and 4 + lk) and target
+        // (past the end the last row again, with dz = 0: nothing that the rows
+        // themselves don't hold, such as 0 times an infinite weight, gets into the sums)
         const int64_t r = tile * TR + li;
         const bool ok = r < n;
-        const int64_t row = ok ? (idx ? (int64_t)idx[r] : r) : 0;
+        const int64_t rc = ok ? r : n - 1, row = idx ? (int64_t)idx[rc] : rc;
         float a1[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const int c = 4 * ks + lk;
-            a1[ks] = (ok && c < NF) ? (X[row * NF + c] - mean[ks]) * istd[ks] : 0.f;
+            a1[ks] = c < NF ? (X[row * NF + c] - mean[ks]) * istd[ks] : 0.f;
         }
-        const float yr = ok ? y[row] : 0.f;
+        const float yr = y[row];
         float h[3][4];
         f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -269,7 +271,7 @@ __global__ void __launch_bounds__(256) k_train(const float *__restrict__ P, cons
         z += __shfl_xor(z, 32);
         z += b4;
         const float res = ok ? softplusf(z) - yr : 0.f;
-        const float dz = two_n * res / (1.f + expf(-z));
+        const float dz = ok ? two_n * res / (1.f + expf(-z)) : 0.f;
         if (l < 16) {
             r2 += res * res;
             gb4 += dz;
