@@ -42,7 +42,7 @@ constexpr size_t kAlign = 256;
 struct Plan {
     size_t total = 0;
     size_t tabD, tabF, tabW, geoD, geoW, pcode, bpos, xyz, wJ, J, Gm, invw, invMb, bmap, bown, goff, gmem, ftag,
-        wallu, f[4], rtb, rhoc, Fn, io, red, flag, posmap, hidx, nbr = 0, tabL, aff = 0, nodes = 0, rtb2 = 0, rhoc2 = 0, cl_params = 0, cl_X = 0, cl_dtau = 0;
+        wallu, f[4], rtb, rhoc, Fn, io, red, flag, posmap, hidx, nbr = 0, tabL = 0, aff = 0, nodes = 0, rtb2 = 0, rhoc2 = 0, cl_params = 0, cl_X = 0, cl_dtau = 0;
     int nred = 0;
     bool closure = false;
 };
@@ -112,7 +112,7 @@ Plan make_plan(const sel_mesh *m, const sel_params *p)
     L.tabD = carve(c, ts * n1 * n1);
     L.tabF = carve(c, ts * n1 * n1);
     L.tabW = carve(c, ts * n1);
-    L.tabL = carve(c, ts * sel::kLineTab);
+    if (m->dim == 3) L.tabL = carve(c, ts * sel::kLineTab);
     if (!m->aff.empty()) L.aff = carve(c, ts * m->aff.size());
     L.geoD = carve(c, 8 * n1 * n1);
     L.geoW = carve(c, 8 * n1);
@@ -190,13 +190,11 @@ int upload_tables(sel_sim *s, const sel::Tables &t, const sel_mesh *m, std::vect
     if (put(s->tabW, Wt.data(), sizeof(T) * Wt.size())) return SEL_EDEVICE;
     if (put(s->geoD, D.data(), 8 * D.size())) return SEL_EDEVICE;
     if (put(s->geoW, W.data(), 8 * W.size())) return SEL_EDEVICE;
-    double lt[sel::kLineTab] = {};
-    const int nlt = sel::find_ops(m->dim, m->N, s->Q, s->prec)->line_tables(t, lt);
-    std::vector<T> Lt = conv<T>(lt, nlt);
-    if (put(s->tabL, Lt.data(), sizeof(T) * Lt.size())) return SEL_EDEVICE;
-    if (s->aff) {
-        std::vector<T> Af = conv<T>(m->aff.data(), m->aff.size());
-        if (put(s->aff, Af.data(), sizeof(T) * Af.size())) return SEL_EDEVICE;
+    if (s->tabL) {
+        double lt[sel::kLineTab] = {};
+        const int nlt = sel::find_ops(m->dim, m->N, s->Q, s->prec)->line_tables(t, lt);
+        std::vector<T> Lt = conv<T>(lt, nlt);
+        if (put(s->tabL, Lt.data(), sizeof(T) * Lt.size())) return SEL_EDEVICE;
     }
     std::vector<T> wu = conv<T>(m->wall_u.data(), m->wall_u.size());
     if (put(s->wallu, wu.data(), sizeof(T) * wu.size())) return SEL_EDEVICE;
@@ -254,6 +252,32 @@ static __global__ void __launch_bounds__(256) k_bin_sums(const double *terms, in
         out[b] = sh[0][0];
         out[nbins + b] = sh[1][0];
     }
+}
+
+// FP64 values in the storage type
+template <typename T>
+static __global__ void __launch_bounds__(256) k_convert(const double *src, T *dst, int64_t n)
+{
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q < n) dst[q] = T(src[q]);
+}
+
+// node table of the 2D stage kernels: interior slot or group, contribution
+// slot, members of the group (0: interior) and owner, extra rank index
+static __global__ void __launch_bounds__(256) k_node_table(const int32_t *pcode, const int32_t *bmap, const uint8_t *bown,
+                                                           const int32_t *posmap, const int32_t *goff,
+                                                           const int32_t *hidx, int64_t nl, int np, int nbe, int4 *nodes)
+{
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= nl) return;
+    const int pc = pcode[q % np];
+    int4 nd{pc, 0, 0, 0};
+    if (pc < 0) {
+        const int64_t lb = q / np * nbe - pc - 1;
+        const int32_t g = bmap[lb], h = hidx[g];
+        nd = int4{g, posmap[lb], (goff[g + 1] - goff[g]) | (bown[lb] ? sel::kOwn : 0), h < 0 ? 0 : h};
+    }
+    nodes[q] = nd;
 }
 
 static void free_profile(sel_sim *s)
@@ -351,7 +375,7 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     s->tabD = b + L.tabD;
     s->tabF = b + L.tabF;
     s->tabW = b + L.tabW;
-    s->tabL = b + L.tabL;
+    if (m->dim == 3) s->tabL = b + L.tabL;
     if (!m->aff.empty()) s->aff = b + L.aff;
     s->geoD = reinterpret_cast<double *>(b + L.geoD);
     s->geoW = reinterpret_cast<double *>(b + L.geoW);
@@ -422,27 +446,26 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     UP(s->gmem, m->gmem.data(), 4 * m->gmem.size());
     UP(s->ftag, m->ftag.data(), 4 * m->ftag.size());
     UP(s->posmap, m->posmap.data(), 4 * m->posmap.size());
-    std::vector<int4> nodes;
-    if (s->nodes) {
-        // node table of the 2D stage kernels: interior slot or group, contribution
-        // slot, members of the group (0: interior) and owner, extra rank index
-        nodes.resize((size_t)nl);
-        for (int64_t e = 0; e < m->E; ++e)
-            for (int q = 0; q < m->np; ++q) {
-                const int pc = m->pcode[q];
-                if (pc >= 0) {
-                    nodes[e * m->np + q] = int4{pc, 0, 0, 0};
-                    continue;
-                }
-                const int64_t lb = e * m->nbe - pc - 1;
-                const int32_t g = m->bmap[lb];
-                nodes[e * m->np + q] = int4{g, m->posmap[lb], (m->goff[g + 1] - m->goff[g]) | (m->bown[lb] ? sel::kOwn : 0),
-                                            m->hidx[g] < 0 ? 0 : m->hidx[g]};
-            }
-        UP(s->nodes, nodes.data(), sizeof(int4) * nodes.size());
-    }
     if (m->dg) UP(s->nbr, m->nbr.data(), 4 * m->nbr.size());
     UP(s->hidx, m->hidx.data(), 4 * m->hidx.size());
+    // what grows with the mesh is laid out on the device, with no host copy: the
+    // affine constants (through the transfer buffer) and the node table
+    if (s->aff) {
+        const int64_t na = (int64_t)m->aff.size();
+        UP(s->io, m->aff.data(), 8 * na);
+        const dim3 grid((unsigned)((na + 255) / 256));
+        if (s->prec == SEL_FP32_DEV)
+            hipLaunchKernelGGL(k_convert<float>, grid, dim3(256), 0, s->stream, s->io, static_cast<float *>(s->aff), na);
+        else
+            hipLaunchKernelGGL(k_convert<double>, grid, dim3(256), 0, s->stream, s->io, static_cast<double *>(s->aff), na);
+    }
+    if (s->nodes)
+        hipLaunchKernelGGL(k_node_table, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s->stream, s->pcode, s->bmap,
+                           s->bown, s->posmap, s->goff, s->hidx, nl, m->np, m->nbe, s->nodes);
+    if (hipGetLastError() != hipSuccess) {
+        set_error("sel_init: launch failed");
+        return fail(SEL_EDEVICE);
+    }
     UP(s->io, rho, 8 * nl);
     UP(s->io + nl, u, 8 * nl * m->dim);
 #undef UP

@@ -98,7 +98,7 @@ struct sel_sim {
     double time = 0.0;
     int64_t nstep = 0;
     // device pointers (typed views of the workspace)
-    void *tabL = nullptr;      // T: mirrored line tables (LineTab), derivative then filter - identity
+    void *tabL = nullptr;      // 3D, T: mirrored line tables (LineTab), derivative then filter - identity
     void *aff = nullptr;       // T [E][10]: dr_m/dx_k and J of each element when all are affine, else nullptr
     void *tabD = nullptr, *tabF = nullptr, *tabW = nullptr;  // T tables [n1*n1], [n1*n1], [n1]
     double *geoD = nullptr, *geoW = nullptr;                  // FP64 D-hat and GLL weights
