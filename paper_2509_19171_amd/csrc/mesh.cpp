@@ -376,32 +376,39 @@ static int mesh_create(int32_t dim, int32_t N, int64_t E, const double *xyz, con
     return SEL_OK;
 }
 
-// Affine elements: x = x_0 + sum_m a_m (r_m + 1), a_m half the edge from node 0
-// to the last node along r_m, at every node up to a few roundings of the
+// Affine elements (3D): x = x_0 + sum_m a_m (r_m + 1), a_m half the edge from node
+// 0 to the last node along r_m, at every node up to a few roundings of the
 // element's coordinates (8 units of 2^-52 of their magnitude). The metric
 // of such an element is constant up to the rounding that it has anyway when it
 // is differentiated node by node. One element off this leaves the list empty.
 static void find_affine(sel_mesh *m)
 {
     sel::Tables t;
-    if (sel::build_gll(m->N, t)) return;
-    const int d = m->dim, n1 = m->n1, N = m->N;
+    if (m->dim != 3 || sel::build_gll(m->N, t)) return;
+    const int n1 = m->n1, N = m->N;
     const int str[3] = {1, n1, n1 * n1};
     std::vector<double> out((size_t)m->E * 10, 0.0);
     for (int64_t e = 0; e < m->E; ++e) {
-        const double *x = m->xyz.data() + e * m->np * d;
-        double a[3][3] = {}, mag = 0.0;
-        for (int r = 0; r < d; ++r)
-            for (int c = 0; c < d; ++c) a[r][c] = 0.5 * (x[(int64_t)N * str[r] * d + c] - x[c]);
-        for (int64_t q = 0; q < (int64_t)m->np * d; ++q) mag = std::max(mag, std::fabs(x[q]));
-        const double tol = 8.0 * 0x1p-52 * mag;
-        for (int p = 0; p < m->np; ++p)
-            for (int c = 0; c < d; ++c) {
-                double v = x[c];
-                for (int r = 0; r < d; ++r) v += a[r][c] * (t.xi[(p / str[r]) % n1] + 1.0);
-                if (!(std::fabs(v - x[(int64_t)p * d + c]) <= tol)) return;
+        const double *x = m->xyz.data() + e * m->np * 3;
+        double a[3][3], off[3][sel::kMaxN1][3];  // off: a_r (xi + 1) along each direction
+        for (int r = 0; r < 3; ++r)
+            for (int c = 0; c < 3; ++c) {
+                a[r][c] = 0.5 * (x[(int64_t)N * str[r] * 3 + c] - x[c]);
+                for (int i = 0; i < n1; ++i) off[r][i][c] = a[r][c] * (t.xi[i] + 1.0);
             }
-        if (d == 2) a[2][2] = 1.0;
+        double mag = 0.0, dev = 0.0;
+        bool ok = true;
+        const double *y = x;
+        for (int k = 0; k < n1 && ok; ++k)
+            for (int j = 0; j < n1; ++j)
+                for (int i = 0; i < n1; ++i, y += 3)
+                    for (int c = 0; c < 3; ++c) {
+                        const double d = std::fabs(x[c] + off[0][i][c] + off[1][j][c] + off[2][k][c] - y[c]);
+                        mag = std::max(mag, std::fabs(y[c]));
+                        dev = d > dev ? d : dev;
+                        ok &= d == d;  // NaN
+                    }
+        if (!ok || !(dev <= 8.0 * 0x1p-52 * mag)) return;
         // dr_m/dx = (a_{m+1} x a_{m+2}) / J
         double cx[3][3], J = 0.0;
         for (int r = 0; r < 3; ++r) {
