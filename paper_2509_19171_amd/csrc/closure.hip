@@ -50,9 +50,9 @@ __device__ __forceinline__ float guard_dtau(float d, float tau, float dmax)
 // (two buffers of 8.5 KB, one barrier per layer), so that five workgroups share a
 // CU and the tanh of some runs under the matrix products of others. Bound by
 // the matrix units (14.5 us for 131 k rows) and the tanh (9 us), which overlap
-// little, and the last of 4 rounds of tiles: 131 k rows 36.5 -> 34.6 us, 14 k rows
-// 10.7 -> 8.8, against weights in LDS (71 KB, two workgroups per CU). Tiles of 16
-// rows 39, of 64 rows 36.8.
+// little. Tiles of 16 rows took 39 us for 131 k rows, of 64 rows 36.8, these 34.6.
+// Few rows and sizes that leave k_mlp_lds a nearly empty last round take this
+// kernel (mlp_in_lds).
 constexpr int RW = 32;  // rows per tile
 constexpr int RT = RW / 16;
 // five resident workgroups per CU, each looping over its tiles
@@ -137,6 +137,203 @@ __global__ void __launch_bounds__(256, 5) k_mlp(const float *__restrict__ P, con
             if (zout) zout[r] = zr;
             if (dtau) dtau[r] = guard_dtau(tau * softplusf(zr), tau, dmax);
         }
+    }
+}
+
+// The network with its weights in LDS: each wavefront runs tiles of RW rows
+// of its own through all layers (A = activations, B = W^T, 2 x 4 output tiles of
+// 16 x 16, activations re-laid out through LDS between layers). 71 KB of LDS,
+// so two workgroups share a CU. A wavefront's LDS operations complete in order,
+// so inside the row loop only compiler scheduling barriers separate the layers
+// and the four wavefronts of a workgroup run independently. At most 1024
+// workgroups, each looping over its tiles, so that one stages the weights
+// for many tiles (4096 workgroups took 1.3% longer on 1.4 M rows).
+constexpr int64_t kLdsBlocks = 1024;
+
+// W2 and W3 into LDS by a workgroup of 256 threads: every load of a thread is
+// issued before its first LDS store, so the workgroup waits for one memory
+// round trip instead of one per loop iteration.
+__device__ __forceinline__ void stage_hidden(const float *__restrict__ P, float (*sW2)[NH + 1],
+                                             float (*sW3)[NH + 1], int tid)
+{
+    constexpr int PER = NH * NH / 256;
+    float a[PER], b[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        a[i] = P[OFF_W2 + tid + 256 * i];
+        b[i] = P[OFF_W3 + tid + 256 * i];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int q = tid + 256 * i;
+        sW2[q / NH][q % NH] = a[i];
+        sW3[q / NH][q % NH] = b[i];
+    }
+}
+
+__global__ void __launch_bounds__(256) k_mlp_lds(const float *__restrict__ P, const float *__restrict__ X, int64_t n,
+                                                 float tau, float *__restrict__ zout, float *__restrict__ dtau)
+{
+    __shared__ float sW1[NH][9];
+    __shared__ float sW2[NH][NH + 1];
+    __shared__ float sW3[NH][NH + 1];
+    __shared__ float sb1[NH], sb2[NH], sb3[NH], sw4[NH];
+    __shared__ float sH[4][RW][NH + 1];
+    __shared__ float smean[NF], sistd[NF];
+    const int tid = threadIdx.x;
+    const float b4 = P[OFF_B4], dmax = P[OFF_DMAX];
+    {
+        // all loads first (one round trip), then the LDS stores
+        float w1v[2], bv[4] = {0.f, 0.f, 0.f, 0.f}, mv = 0.f, sv = 1.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = tid + 256 * i, r = q / 8, c = q % 8;
+            w1v[i] = (c < NF) ? P[OFF_W1 + r * NF + c] : 0.f;
+        }
+        if (tid < NH) {
+            bv[0] = P[OFF_B1 + tid];
+            bv[1] = P[OFF_B2 + tid];
+            bv[2] = P[OFF_B3 + tid];
+            bv[3] = P[OFF_W4 + tid];
+        }
+        if (tid < NF) {
+            mv = P[OFF_MEAN + tid];
+            sv = P[OFF_STD + tid];
+        }
+        stage_hidden(P, sW2, sW3, tid);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = tid + 256 * i;
+            sW1[q / 8][q % 8] = w1v[i];
+        }
+        if (tid < NH) {
+            sb1[tid] = bv[0];
+            sb2[tid] = bv[1];
+            sb3[tid] = bv[2];
+            sw4[tid] = bv[3];
+        }
+        if (tid < NF) {
+            smean[tid] = mv;
+            sistd[tid] = 1.f / sv;
+        }
+    }
+    __syncthreads();
+    const int w = tid / 64, l = tid % 64;
+    const int li = l & 15, lk = l >> 4;
+    for (int64_t base = (int64_t)blockIdx.x * (4 * RW); base < n; base += (int64_t)gridDim.x * (4 * RW)) {
+        // normalised inputs, K padded to 8: lane l fills row l % RW, columns 4 (l / RW) .. +3
+        {
+            const int rr = l % RW, c0 = 4 * (l / RW);
+            const int64_t r = base + w * RW + rr;
+#pragma unroll
+            for (int c = c0; c < c0 + 4; ++c) {
+                sH[w][rr][c] = (c < NF && r < n) ? (X[r * NF + c] - smean[c]) * sistd[c] : 0.f;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        f4 acc[RT][4];
+        // hidden layer 1 (K = 8)
+#pragma unroll
+        for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            float a[RT], b[4];
+#pragma unroll
+            for (int t = 0; t < RT; ++t) a[t] = sH[w][16 * t + li][4 * ks + lk];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b[t] = sW1[16 * t + li][4 * ks + lk];
+#pragma unroll
+            for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < 4; ++tj)
+                    acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int col = 16 * tj + li;
+                    sH[w][16 * ti + 4 * lk + q][col] = tanh_fast(acc[ti][tj][q] + sb1[col]);
+                }
+        __builtin_amdgcn_wave_barrier();
+        // hidden layers 2 and 3 (K = 64)
+#pragma unroll
+        for (int layer = 0; layer < 2; ++layer) {
+            const float(*Wl)[NH + 1] = layer == 0 ? sW2 : sW3;
+            const float *bl = layer == 0 ? sb2 : sb3;
+#pragma unroll
+            for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < NH / 4; ++ks) {
+                float a[RT], b[4];
+#pragma unroll
+                for (int t = 0; t < RT; ++t) a[t] = sH[w][16 * t + li][4 * ks + lk];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) b[t] = Wl[16 * t + li][4 * ks + lk];
+#pragma unroll
+                for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+                    for (int tj = 0; tj < 4; ++tj)
+                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+                for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int col = 16 * tj + li;
+                        sH[w][16 * ti + 4 * lk + q][col] = tanh_fast(acc[ti][tj][q] + bl[col]);
+                    }
+            __builtin_amdgcn_wave_barrier();
+        }
+        // output layer: two lanes per row, halves of the 64 products
+        {
+            const int rr = l % RW, h = l / RW;
+            float z = 0.f;
+#pragma unroll 8
+            for (int c = 32 * h; c < 32 * h + 32; ++c) z += sH[w][rr][c] * sw4[c];
+            z += __shfl_xor(z, 32);
+            z += b4;
+            const int64_t r = base + w * RW + rr;
+            if (h == 0 && r < n) {
+                if (zout) zout[r] = z;
+                if (dtau) dtau[r] = guard_dtau(tau * softplusf(z), tau, dmax);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Which of the two kernels takes n rows. k_mlp_lds deals 128 rows at a time to
+// the 256 CUs and takes about 5.8 us for each such round of 32 k rows, k_mlp 32
+// rows at a time and 1.5 us per 8 k rows: whichever has less to do in whole
+// rounds, and the former for its slightly better rate (2 to 3%) where both have
+// many. Measured, us with k_mlp_lds and k_mlp: 8 k rows 9.7 and 5.3, 16 k 9.8 and
+// 7.6, 32 k 9.8 and 11.8, 33 k 14.9 and 13.0, 64 k 15.3 and 17.5, 98.4 k 27.5 and 24.7,
+// 131.0 k 28.4 and 30.3, 131.3 k 33.2 and 31.5, 262 k 51.8 and 54.3, 1.4 M 261 and 270.
+constexpr bool mlp_in_lds(int64_t n)
+{
+    return 4 * ((n + 32767) / 32768) <= (n + 8191) / 8192 + 1 + n / (1 << 19);
+}
+
+void launch_mlp(const float *P, const float *X, int64_t n, float tau, float *z, float *dtau, hipStream_t st)
+{
+    if (mlp_in_lds(n)) {
+        const int64_t nb = (n + 4 * RW - 1) / (4 * RW);
+        hipLaunchKernelGGL(k_mlp_lds, dim3((unsigned)(nb < kLdsBlocks ? nb : kLdsBlocks)), dim3(256), 0, st, P, X, n,
+                           tau, z, dtau);
+    } else {
+        const int64_t nb = (n + RW - 1) / RW;
+        hipLaunchKernelGGL(k_mlp, dim3((unsigned)(nb < kInferMaxBlocks ? nb : kInferMaxBlocks)), dim3(256), 0, st, P, X,
+                           n, tau, z, dtau);
     }
 }
 
@@ -644,10 +841,7 @@ int check_pair(const sel_sim *f, const sel_sim *c)
 int launch_mlp_infer(sel_sim *s)
 {
     const int64_t n = s->Gtot;
-    int64_t nb = (n + RW - 1) / RW;
-    if (nb > kInferMaxBlocks) nb = kInferMaxBlocks;
-    hipLaunchKernelGGL(k_mlp, dim3((unsigned)nb), dim3(256), 0, s->stream, s->cl_params, s->cl_X, n, float(s->tau),
-                       nullptr, s->cl_dtau);
+    launch_mlp(s->cl_params, s->cl_X, n, float(s->tau), nullptr, s->cl_dtau, s->stream);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
         set_error(std::string("closure inference launch failed: ") + hipGetErrorString(err));
@@ -773,10 +967,7 @@ extern "C" int sel_mlp_forward(const float *d_params, const float *d_X, int64_t 
         return SEL_EINVAL;
     }
     if (n == 0) return SEL_OK;
-    int64_t nb = (n + sel::RW - 1) / sel::RW;
-    if (nb > sel::kInferMaxBlocks) nb = sel::kInferMaxBlocks;
-    hipLaunchKernelGGL(sel::k_mlp, dim3((unsigned)nb), dim3(256), 0, static_cast<hipStream_t>(stream), d_params, d_X,
-                       n, float(tau), d_z, d_dtau);
+    sel::launch_mlp(d_params, d_X, n, float(tau), d_z, d_dtau, static_cast<hipStream_t>(stream));
     if (hipGetLastError() != hipSuccess) {
         set_error("sel_mlp_forward: launch failed");
         return SEL_EDEVICE;
