@@ -22,7 +22,7 @@ struct BigGeo {
     static_assert(R * BLOCK >= NP && BLOCK <= 1024, "every node has a thread");
 };
 
-template <int N, int Q, typename T, int MODE>
+template <int N, int Q, typename T, int MODE, bool FN = false>
 __global__ void __launch_bounds__(BigGeo<N>::BLOCK) k_stage_big(StageArgs<T> A)
 {
     using BG = BigGeo<N>;
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(BigGeo<N>::BLOCK) k_stage_big(StageArgs<T> A)
                 if constexpr (PF) f0v = f0[r];
                 else f0v = A.f0in[si[r].base + (int64_t)a * si[r].stride];
                 T L = rt * invw[r] + A.fsc[a] * rho[r];
-                if (A.Fn) {
+                if constexpr (FN) {
                     const T *F = A.Fn + 3 * gix[r];
                     L += T(3.0 * lat_t<DIM, Q>(a)) *
                          edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(F[0], F[1], F[2]);

@@ -385,9 +385,12 @@ struct StageArgs {
     const T *Fn;          // force density per node id [Gtot][3], added to rho g (nullptr: none)
 };
 
-// DGC: the discontinuous coupling's interface flux is compiled in (a
-// separate instantiation, so the continuous kernels carry none of it).
-template <int DIM, int N, int Q, typename T, bool DEV, int MODE, bool DGC = false>
+// DGC: the discontinuous coupling's interface flux is compiled in, FN: the
+// force per node is (separate instantiations: the plain kernels carry none of
+// it. Carried along with a zero force it cost registers: FP32 stage of 1024
+// elements N = 3 25.6 -> 27.1 us, a step at N = 5 125 -> 136; behind a test in the
+// kernel a 2D stage took 7.9 instead of 7.4).
+template <int DIM, int N, int Q, typename T, bool DEV, int MODE, bool DGC = false, bool FN = false>
 __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && sizeof(T) == 4) ? 4 : 1)) k_stage(StageArgs<T> A)
 {
     using GG = Geo<DIM, N>;
@@ -607,7 +610,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
 
     T rho = 0;
     T Fv[3] = {T(0), T(0), T(0)};
-    if (A.Fn && valid) {
+    if (FN && valid) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) Fv[c] = A.Fn[3 * gix + c];
     }
@@ -615,7 +618,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
         if (valid) {
             T om = A.omega;
             if (A.dtau) om = T(1) / (A.tau + T(A.dtau[gix]) + T(0.5));
-            collide_node<DIM, Q, T, DEV>(fq, A.rho0, om, A.dt, A.g, rho, Fv, A.Fn != nullptr);
+            collide_node<DIM, Q, T, DEV>(fq, A.rho0, om, A.dt, A.g, rho, Fv, FN);
             if (own) {
                 static_for<0, Q>([&](auto AA) {
                     constexpr int a = decltype(AA)::value;
@@ -697,10 +700,11 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
         constexpr int a = decltype(AA)::value;
         // L at an interior node: volume term over the mass, and F*
         auto total = [&](T rt) {
-            // (without a force per node Fv is zero: a test here took 0.5 us of 7)
-            return rt * invw + A.fsc[a] * rho +
-                   T(3.0 * lat_t<DIM, Q>(a)) *
-                       edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(Fv[0], Fv[1], Fv[2]);
+            T L = rt * invw + A.fsc[a] * rho;
+            if constexpr (FN)
+                L += T(3.0 * lat_t<DIM, Q>(a)) *
+                     edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(Fv[0], Fv[1], Fv[2]);
+            return L;
         };
         T rt = stream_volume<DIM, N, Q, a, DIF>(P, v, Di, Dj, Dk, Gr, rowr, rows, rowt);
         if (wcode) {

@@ -49,7 +49,7 @@ __device__ __forceinline__ int interior_node(int s)
 
 }  // namespace mfk
 
-template <int Q>
+template <int Q, bool FN = false>
 __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
 {
     using namespace mfk;
@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
     __shared__ __attribute__((aligned(16))) float pl[PLN];
     __shared__ float xb[8][2][128];  // per wavefront: r- and s-derivatives of a velocity pair
     __shared__ float sfs[Q];  // F* per unit density of each velocity
-    __shared__ float sfe[Q][3];  // 3 t_a e_a (force per node)
+    __shared__ float sfe[FN ? Q : 1][3];  // 3 t_a e_a (force per node)
 
     const int tid = threadIdx.x;
     const int64_t e = xcd_block(A.nblk);
@@ -83,9 +83,8 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
         constexpr int a = decltype(AA)::value;
         if (tid == a) {
             sfs[a] = A.fsc[a];
-            sfe[a][0] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, 0));
-            sfe[a][1] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, 1));
-            sfe[a][2] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, 2));
+            if constexpr (FN)
+                for (int c = 0; c < 3; ++c) sfe[a][c] = float(3.0 * lat_t<DIM, Q>(a) * lat_e<DIM, Q>(a, c));
         }
     });
 
@@ -265,7 +264,7 @@ __global__ void __launch_bounds__(512, 4) k_stage23_mf(StageArgs<float> A)
                     const mf4 rt = *reinterpret_cast<const mf4 *>(pl + (a - 1) * NP + s0);
                     L = rt * iw4[s0 / 4] + fs * rh;
                 }
-                if (A.Fn) {
+                if constexpr (FN) {
                     // [4 slots][3] as three vectors
                     const mf4 *F4 = reinterpret_cast<const mf4 *>(A.Fn + 3 * (e * NI + s0));
                     const mf4 u = F4[0], v = F4[1], x = F4[2];

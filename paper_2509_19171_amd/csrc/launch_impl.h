@@ -253,7 +253,14 @@ struct Impl {
                 return SEL_EUNSUPPORTED;
             }
             if (int rc = tic(s, kind, ev)) return rc;
-            hipLaunchKernelGGL((k_stage_big<N, Q, T, MODE>), grid, dim3(BigGeo<N>::BLOCK), 0, s->stream, A);
+            bool fn = false;
+            if constexpr (MODE == M_STAGE23) {
+                fn = A.Fn != nullptr;
+                if (fn)
+                    hipLaunchKernelGGL((k_stage_big<N, Q, T, MODE, true>), grid, dim3(BigGeo<N>::BLOCK), 0, s->stream, A);
+            }
+            if (!fn)
+                hipLaunchKernelGGL((k_stage_big<N, Q, T, MODE>), grid, dim3(BigGeo<N>::BLOCK), 0, s->stream, A);
         } else {
             if (int rc = tic(s, kind, ev)) return rc;
             // element contributions under the discontinuous coupling carry the
@@ -269,9 +276,17 @@ struct Impl {
             if (!dg) {
                 // FP32 3D order 7, later stages: vector loads and matrix-core contractions
                 if constexpr (kMfma && MODE == M_STAGE23) {
-                    hipLaunchKernelGGL((k_stage23_mf<Q>), grid, block, 0, s->stream, A);
+                    if (A.Fn) hipLaunchKernelGGL((k_stage23_mf<Q, true>), grid, block, 0, s->stream, A);
+                    else hipLaunchKernelGGL((k_stage23_mf<Q>), grid, block, 0, s->stream, A);
                 } else {
-                    hipLaunchKernelGGL((k_stage<DIM, N, Q, T, DEV, MODE>), grid, block, 0, s->stream, A);
+                    bool fn = false;
+                    if constexpr (MODE == M_STAGE1 || MODE == M_STAGE23) {
+                        fn = A.Fn != nullptr;
+                        if (fn)
+                            hipLaunchKernelGGL((k_stage<DIM, N, Q, T, DEV, MODE, false, true>), grid, block, 0,
+                                               s->stream, A);
+                    }
+                    if (!fn) hipLaunchKernelGGL((k_stage<DIM, N, Q, T, DEV, MODE>), grid, block, 0, s->stream, A);
                 }
             }
         }
