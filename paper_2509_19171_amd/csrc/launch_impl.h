@@ -294,6 +294,26 @@ struct Impl {
         return toc(s, ev);
     }
 
+    // Wavefronts that share 64 groups of the assembly. Four hide more latency as
+    // long as all their workgroups are resident at once (8 per CU in FP32, 5 for
+    // D3Q19 in FP64), two have fewer to run after that, except where they end in a
+    // round (8 per CU, 7 for D3Q27) that is less than a third full. us with 2 and 4:
+    // FP32 D3Q27 61 k groups 15.1 and 12.1, 127 k 17.7 and 15.5, 152 k 19.3 and 21.4,
+    // 219 k 23.4 and 24.8, 250 k 32.1 and 27.8, 417 k 48.6 and 51.0, 520 k 56.7 and 55.0;
+    // FP64 D3Q19 65 k 14.5 and 13.0, 127 k 20.0 and 22.7, 169 k 30.6 and 28.8. FP64
+    // D3Q27 with two spills (152 k 54 and 38). With the discontinuous coupling each
+    // of them looks up the faces: 33 k groups 9.8 and 9.3, 152 k 17.7 and 19.6.
+    static constexpr bool kSplit2 = !(Q == 27 && sizeof(T) == 8);
+    static int assembly_split(int64_t n, bool dg)
+    {
+        constexpr int64_t cu = 256;
+        if (dg) return n <= 160 * cu ? 4 : 2;
+        if (!kSplit2) return 4;
+        constexpr int64_t r4 = 64 * cu * (sizeof(T) == 4 ? 8 : 5);
+        constexpr int64_t r2 = sizeof(T) == 8 ? 2 * r4 : 128 * cu * (Q == 27 ? 7 : 8);
+        return n <= r4 || (n > r2 && (sizeof(T) == 8 || 40 * (n % r2) < 13 * r2)) ? 4 : 2;
+    }
+
     static int launch_group(sel_sim *s, const GroupArgs<T> &B)
     {
         if (s->ngrp == 0) return SEL_OK;
@@ -301,18 +321,16 @@ struct Impl {
         hipEvent_t ev = nullptr;
         if (int rc = tic(s, 2, ev)) return rc;
         // the discontinuous coupling adds its interface flux here
-        // wavefronts per 64 groups: four fill the chip sooner on small meshes
-        // (D3Q27 FP32, us with 2 and 4: 8^3 elements N = 3 10.8 and 7.9, 1024
-        // elements N = 5 13.9 and 10.6, 16^3 N = 7 55 and 53.5) and cost nothing on
-        // large ones; two on large meshes with the discontinuous coupling, which
-        // looks up its faces per thread (10^3 N = 5, 152 k groups, 15.6 and 17.8)
-        const dim3 grid((unsigned)xcd_grid((s->ngrp * (B.nbr && s->ngrp > (1 << 16) ? 2 : 4) + 255) / 256));
-        if (B.nbr && s->ngrp <= (1 << 16)) {
+        const int split = assembly_split(s->ngrp, B.nbr != nullptr);
+        const dim3 grid((unsigned)xcd_grid((s->ngrp * split + 255) / 256));
+        if (B.nbr && split == 4) {
             hipLaunchKernelGGL((k_group_split<Q, T, 4, N>), grid, block, 0, s->stream, B);
         } else if (B.nbr) {
             hipLaunchKernelGGL((k_group_split<Q, T, 2, N>), grid, block, 0, s->stream, B);
-        } else {
+        } else if (split == 4) {
             hipLaunchKernelGGL((k_group_split<Q, T, 4>), grid, block, 0, s->stream, B);
+        } else if constexpr (kSplit2) {
+            hipLaunchKernelGGL((k_group_split<Q, T, 2>), grid, block, 0, s->stream, B);
         }
         SEL_LAUNCH_CHECK();
         return toc(s, ev);
