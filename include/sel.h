@@ -164,9 +164,10 @@ int sel_step(sel_sim *sim, int64_t nsteps);
 /* Same as sel_step, with HIP events recorded on the stream around every
  * kernel launch. On return (it synchronises) ms[k] holds the summed device
  * time and launches[k] the number of launches of kernel kind k:
- *   0 filter of the previous step and collision (2D: first-stage kernel, which
- *     also streams), 1 streaming operator of a stage (2D: of the later stages),
- *   2 shared-node assembly, 3 end-of-call filter, 4 closure features,
+ *   0 filter of the previous step and collision (where one kernel takes the
+ *     whole first stage: with its streaming), 1 streaming operator of a stage,
+ *   2 shared-node assembly, 3 filter alone (end of the call, or ahead of a first
+ *     stage that does not take it along), 4 closure features,
  *   5 closure network (both only with a closure attached). ms and launches
  *   hold SEL_NKIND entries. */
 #define SEL_NKIND 6

@@ -353,8 +353,10 @@ __device__ __forceinline__ void interface_flux(T &rt, T v, const T (&Gr)[DIM][DI
 }
 
 // ----------------------------------------------------------- stage kernel --
-// M_STAGE1 (filter and collision) and M_FILTER serve 2D alone, with M_STAGE23
-// for the discontinuous coupling; 3D takes M_STAGE23 for curved elements.
+// M_STAGE1 is the first stage in one kernel: a pending filter (2D, 3D up to order
+// kFusedFilter3), collision and streaming. M_FILTER serves 2D alone.
+// (Impl::first_stage says which 3D meshes take M_STAGE1.)
+constexpr int kFusedFilter3 = 3;
 enum { M_STAGE1 = 0, M_STAGE23 = 1, M_LOCAL = 2, M_FILTER = 3 };
 
 template <typename T>
@@ -382,6 +384,7 @@ struct StageArgs {
     T tau;                // relaxation time
     const float *dtau;    // learned-closure increments per node id (nullptr: plain method)
     const int32_t *nbr;   // discontinuous coupling: [E][2 dim][(N+1)^(dim-1)] group across each face (nullptr: continuous)
+    int collide_only;     // M_STAGE1: stop after writing the post-collision state
     const T *Fn;          // force density per node id [Gtot][3], added to rho g (nullptr: none)
 };
 
@@ -391,15 +394,16 @@ struct StageArgs {
 // elements N = 3 25.6 -> 27.1 us, a step at N = 5 125 -> 136; behind a test in the
 // kernel a 2D stage took 7.9 instead of 7.4).
 template <int DIM, int N, int Q, typename T, bool DEV, int MODE, bool DGC = false, bool FN = false>
-__global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && sizeof(T) == 4) ? 4 : 1)) k_stage(StageArgs<T> A)
+__global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || MODE == M_STAGE1) && sizeof(T) == 4) ? 4 : 1))
+    k_stage(StageArgs<T> A)
 {
     using GG = Geo<DIM, N>;
     constexpr int n1 = GG::n1, NP = GG::NP, NI = GG::NI, NB = GG::NB, EPB = GG::EPB;
     // collision and filter keep all velocities of the node in registers; the
-    // stages stream the velocities
-    // with a software prefetch one chunk ahead. Velocities are processed in
-    // chunks of NA planes per LDS barrier.
+    // later stages stream the velocities with a software prefetch one chunk
+    // ahead. Velocities are processed in chunks of NA planes per LDS barrier.
     constexpr bool ALLQ = (MODE == M_STAGE1 || MODE == M_FILTER);
+    constexpr bool FILT = ALLQ && (DIM == 2 || N <= kFusedFilter3);
     // FP32: line contractions are taken around the node's own value,
     // sum_q W_q (P_q - x) (+ x for filter rows, which sum to one), so that a
     // large common level of the populations adds no rounding bias (the
@@ -414,10 +418,10 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
     constexpr bool FULL = DIF && EPB == 1 && !ALLQ && Q * NP * 4 <= 80 * 1024;
     // later stages also stage their results through LDS for coalesced stores
     constexpr bool STG = FULL && MODE == M_STAGE23;
-    constexpr int LDS_N = FULL ? Q * NP : 2 * NA * EPB * NP;
+    constexpr int LDS_N = FULL ? Q * NP : (FILT && DIM == 3 ? 3 : 2) * NA * EPB * NP;
     __shared__ __attribute__((aligned(16))) T lds[LDS_N];
     T(*pl)[EPB * NP] = reinterpret_cast<T(*)[EPB * NP]>(lds);
-    __shared__ T sF[ALLQ ? n1 * n1 : 1];
+    __shared__ T sF[FILT ? n1 * n1 : 1];
 
     const int tid = threadIdx.x;
     const int le = tid / NP;
@@ -427,7 +431,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
     const int64_t e = eb * EPB + le;
     const bool valid = e < A.E;
     const bool filt = (MODE == M_FILTER) || (MODE == M_STAGE1 && A.filter);
-    if constexpr (ALLQ) {
+    if constexpr (FILT) {
         if (filt)
             for (int q = tid; q < n1 * n1; q += GG::BLOCK) sF[q] = A.F[q];
     }
@@ -553,13 +557,13 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
         prefetch(std::integral_constant<int, 0>{});
     }
 
-    if constexpr (ALLQ) {
+    if constexpr (FILT) {
         if (filt) {
             __syncthreads();  // sF visible
             // explicit modal filter (Sec. 2.2.3): (F x F x F) applied one direction at a time
             static_for<0, NC>([&](auto CC) {
                 constexpr int c = decltype(CC)::value;
-                T t1v[NA];
+                T t1v[NA], t2v[NA];
                 static_for<0, NA>([&](auto UU) {
                     constexpr int u = decltype(UU)::value, a = c * NA + u;
                     if constexpr (a < Q) pl[u][base + p] = fq[a];
@@ -592,9 +596,28 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
                             else t2 += sF[j * n1 + q] * pl[NA + u][rows + n1 * q];
                         }
                         if constexpr (DIF) t2 += x;
-                        fq[a] = t2;
+                        t2v[u] = t2;
+                        if constexpr (DIM == 3) pl[2 * NA + u][base + p] = t2;
+                        else fq[a] = t2;
                     }
                 });
+                if constexpr (DIM == 3) {
+                    __syncthreads();
+                    static_for<0, NA>([&](auto UU) {
+                        constexpr int u = decltype(UU)::value, a = c * NA + u;
+                        if constexpr (a < Q) {
+                            const T x = t2v[u];
+                            T t3 = 0;
+#pragma unroll
+                            for (int q = 0; q < n1; ++q) {
+                                if constexpr (DIF) t3 += sF[k * n1 + q] * (pl[2 * NA + u][rowt + n1 * n1 * q] - x);
+                                else t3 += sF[k * n1 + q] * pl[2 * NA + u][rowt + n1 * n1 * q];
+                            }
+                            if constexpr (DIF) t3 += x;
+                            fq[a] = t3;
+                        }
+                    });
+                }
             });
         }
         if constexpr (MODE == M_FILTER) {
@@ -627,7 +650,7 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), ((MODE == M_STAGE23 && s
                 A.rhoc[gix] = rho;
             }
         }
-        return;
+        if (A.collide_only) return;  // whole workgroup
     } else if constexpr (MODE == M_STAGE23) {
         if (valid && inner) rho = A.rhoc[gix];
     }

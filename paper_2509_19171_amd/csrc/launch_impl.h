@@ -240,7 +240,7 @@ struct Impl {
     template <int MODE>
     static int launch_stage(sel_sim *s, const StageArgs<T> &A)
     {
-        static_assert(DIM == 2 || MODE == M_STAGE23 || MODE == M_LOCAL, "3D: launch_relax");
+        static_assert(DIM == 2 || MODE != M_FILTER, "3D: launch_relax");
         if constexpr (DIM == 3 && MODE == M_STAGE23) {
             if (s->aff) return launch_stream(s, A);
         }
@@ -280,7 +280,7 @@ struct Impl {
                     else hipLaunchKernelGGL((k_stage23_mf<Q>), grid, block, 0, s->stream, A);
                 } else {
                     bool fn = false;
-                    if constexpr (MODE == M_STAGE1 || MODE == M_STAGE23) {
+                    if constexpr ((MODE == M_STAGE1 && DIM == 2) || MODE == M_STAGE23) {
                         fn = A.Fn != nullptr;
                         if (fn)
                             hipLaunchKernelGGL((k_stage<DIM, N, Q, T, DEV, MODE, false, true>), grid, block, 0,
@@ -419,19 +419,67 @@ struct Impl {
         return launch_group(s, B);
     }
 
+    // The first stage of a 3D mesh that is not streamed by k_stream, and has the
+    // continuous coupling and no force per node, in one kernel (M_STAGE1)
+    // instead of a collision pass and a streaming pass, or three passes with a filter
+    // pending: the post-collision state is not read back. With few elements it is
+    // the launch that counts; with many the separate kernels hold more
+    // wavefronts, so that FP32 keeps them, while FP64 streams a chunk of
+    // velocities at a time either way. Per step, us, separate and joined, without a
+    // filter: FP64 D3Q27 N = 5 1024 elements 228 and 214, 4096 847 and 819, N = 7 20,480
+    // 9030 and 8640, N = 8 1024 812 and 855 (it spills); N = 4 1024 FP64 134 and 124, FP32
+    // 117 and 108, 16^3 FP64 365 and 386, FP32 220 and 225; N = 7 12^3 FP32 325 and 335.
+    // Filtered: FP64 N = 7 8^3 199 and 187, 20,480 elements 9860 and 9420, N = 5 1024 243 and
+    // 235, 16^3 777 and 802; FP32 N = 5 1024 131 and 132.
+    // Orders up to 3 take the filter along (N = 2 30^3 D3Q19 FP32 277 and 256, N = 3
+    // 24^3 FP64 527 and 514).
+    static constexpr bool kFirst = DIM == 2 || (!kBig && (sizeof(T) == 8 ? !(N == 8 && Q == 27) : N <= 4));
+    static bool first_stage(const sel_sim *s, bool pending)
+    {
+        if (DIM != 3 || !kFirst || s->aff || s->nbr || s->force_on) return false;
+        const int64_t nodes = s->E * NP;
+        if (!pending) return (sizeof(T) == 8 && N >= 5) || nodes <= 200000;
+        if (N <= kFusedFilter3 || N >= 7) return true;
+        return nodes <= (N == 4 ? 160000 : N == 5 ? 225000 : 400000);
+    }
+
     // First stage: filter (when pending) and collide the state S into the
-    // post-collision state y = F0, then FA = y + cc L(y) by a streaming pass like
-    // the later stages'. (2D: the discontinuous coupling alone.)
+    // post-collision state y = F0, then FA = y + cc L(y), by a streaming pass like
+    // the later stages' or in the same kernel (first_stage). (2D: the
+    // discontinuous coupling alone.)
     static int stage_one(sel_sim *s, StageArgs<T> &A, GroupArgs<T> &B, const T *S, T *F0, T *FA, double cc,
                          bool pending)
     {
         if constexpr (DIM == 3) {
+            if constexpr (kFirst) {
+                if (first_stage(s, pending)) {
+                    T *H = st(s, s->cur ^ 1);  // free until the second stage
+                    const bool before = pending && N > kFusedFilter3;
+                    if (before)
+                        if (int rc = launch_relax(s, S, H, true, false, nullptr, false)) return rc;
+                    A.op = before ? H : S;
+                    A.f0out = F0;
+                    A.out = FA;
+                    A.ca = T(0);
+                    A.cb = T(1);
+                    A.cc = T(cc);
+                    A.filter = pending && !before;
+                    if (int rc = launch_stage<M_STAGE1>(s, A)) return rc;
+                    B.f0 = B.fk = F0;
+                    B.out = FA;
+                    B.ca = T(0);
+                    B.cb = T(1);
+                    B.cc = T(cc);
+                    return launch_group(s, B);
+                }
+            }
             if (int rc = launch_relax(s, S, F0, pending, true, A.dtau, s->force_on)) return rc;
             return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
         } else {
             A.op = S;
             A.f0out = F0;
             A.filter = pending ? 1 : 0;
+            A.collide_only = 1;
             if (int rc = launch_stage<M_STAGE1>(s, A)) return rc;
             return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
         }
@@ -738,7 +786,7 @@ struct Impl {
         } else {
         if (op == SEL_OP_COLLIDE) {
             A.f0out = dst;
-            A.out = st(s, s->cur ^ 1);
+            A.collide_only = 1;
             A.filter = 0;
             A.ca = A.cb = A.cc = T(0);
             return launch_stage<M_STAGE1>(s, A);

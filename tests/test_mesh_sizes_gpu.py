@@ -61,3 +61,20 @@ def check(c, steps=2, precs=(("fp64", 1e-12), ("fp32dev", 1e-5)), F=None):
 @pytest.mark.parametrize("Q,nel", [(19, (24, 24, 24)), (19, (27, 27, 27)), (27, (27, 27, 27)), (27, (33, 33, 32))])
 def test_assembly_splits(Q, nel):
     check(curved(box(2, Q, nel)))
+
+
+# the first stage of curved elements: one kernel (small meshes, FP64), the filter
+# in it (N <= 3) or ahead of it, against separate passes
+@pytest.mark.parametrize("filt", [None, "quad"])
+@pytest.mark.parametrize("N,Q", [(2, 27), (3, 19), (4, 27), (5, 19), (6, 27), (7, 27), (8, 19), (8, 27)])
+def test_first_stage_small(N, Q, filt):
+    c = curved(box(N, Q, (3, 2, 2) if N < 6 else (2, 2, 1), filt, walls=True))
+    check(c, 5)
+    check(dataclasses.replace(c, rk="printed4"), 3)
+
+
+@pytest.mark.parametrize("filt", [None, "quad"])
+@pytest.mark.parametrize("N,Q,nel", [(2, 27, (20, 20, 19)), (3, 27, (15, 15, 15)), (4, 27, (12, 12, 12)), (5, 27, (11, 11, 10)),
+                                     (6, 19, (11, 11, 10))])
+def test_first_stage_large(N, Q, nel, filt):
+    check(curved(box(N, Q, nel, filt, walls=True)))
