@@ -897,8 +897,9 @@ struct GroupArgs {
 // The velocities of each group are split between SPLIT wavefronts of a
 // workgroup (uniform in each wavefront), so a thread holds 1/SPLIT of the values
 // and more loads are in flight; the arithmetic of a velocity does not depend on
-// the split.
-template <int A0, int A1, int Q, typename T, int DGN>
+// the split. FN: with a force per node (compiled apart: with it in every kernel
+// the two-way split of FP64 D3Q27 spilled, 54 instead of 39.5 us for 152 k groups).
+template <int A0, int A1, int Q, typename T, int DGN, bool FN>
 __device__ __forceinline__ void group_range(const GroupArgs<T> &A, int64_t g, int nm, int64_t h, T invM, T rho,
                                             const T (&F)[3], SIdx si)
 {
@@ -987,7 +988,7 @@ __device__ __forceinline__ void group_range(const GroupArgs<T> &A, int64_t g, in
         constexpr int a = decltype(AA)::value, u = a - A0;
         const int64_t ix = si.base + (int64_t)a * si.stride;
         T L = sum[u] * invM + A.fsc[a] * rho;
-        if (A.Fn) {
+        if constexpr (FN) {
             constexpr int DIM = (Q == 9) ? 2 : 3;
             L += T(3.0 * lat_t<DIM, Q>(a)) *
                  edot<lat_e<DIM, Q>(a, 0), lat_e<DIM, Q>(a, 1), lat_e<DIM, Q>(a, 2)>(F[0], F[1], F[2]);
@@ -996,7 +997,7 @@ __device__ __forceinline__ void group_range(const GroupArgs<T> &A, int64_t g, in
     });
 }
 
-template <int Q, typename T, int SPLIT, int DGN = 0>
+template <int Q, typename T, int SPLIT, int DGN = 0, bool FN = false>
 __global__ void __launch_bounds__(256) k_group_split(GroupArgs<T> A)
 {
     constexpr int GPB = 256 / SPLIT;  // groups per workgroup
@@ -1012,7 +1013,7 @@ __global__ void __launch_bounds__(256) k_group_split(GroupArgs<T> A)
     const int nm = A.goff[g + 1] - A.goff[g];
     const int64_t h = A.hidx[g];  // (-1 with two members or fewer, then unused)
     T F[3] = {T(0), T(0), T(0)};
-    if (A.Fn) {
+    if constexpr (FN) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) F[c] = A.Fn[3 * (A.Gi + g) + c];
     }
@@ -1021,7 +1022,7 @@ __global__ void __launch_bounds__(256) k_group_split(GroupArgs<T> A)
     const SIdx si = sidx_group(g, Q, A.QGi);
     static_for<0, SPLIT>([&](auto WW) {
         constexpr int k = decltype(WW)::value;
-        if (w % SPLIT == k) group_range<k * Q / SPLIT, (k + 1) * Q / SPLIT, Q, T, DGN>(A, g, nm, h, invM, rho, F, si);
+        if (w % SPLIT == k) group_range<k * Q / SPLIT, (k + 1) * Q / SPLIT, Q, T, DGN, FN>(A, g, nm, h, invM, rho, F, si);
     });
 }
 

@@ -295,23 +295,24 @@ struct Impl {
     }
 
     // Wavefronts that share 64 groups of the assembly. Four hide more latency as
-    // long as all their workgroups are resident at once (8 per CU in FP32, 5 for
-    // D3Q19 in FP64), two have fewer to run after that, except where they end in a
-    // round (8 per CU, 7 for D3Q27) that is less than a third full. us with 2 and 4:
-    // FP32 D3Q27 61 k groups 15.1 and 12.1, 127 k 17.7 and 15.5, 152 k 19.3 and 21.4,
-    // 219 k 23.4 and 24.8, 250 k 32.1 and 27.8, 417 k 48.6 and 51.0, 520 k 56.7 and 55.0;
-    // FP64 D3Q19 65 k 14.5 and 13.0, 127 k 20.0 and 22.7, 169 k 30.6 and 28.8. FP64
-    // D3Q27 with two spills (152 k 54 and 38). With the discontinuous coupling each
-    // of them looks up the faces: 33 k groups 9.8 and 9.3, 152 k 17.7 and 19.6.
-    static constexpr bool kSplit2 = !(Q == 27 && sizeof(T) == 8);
+    // long as all their workgroups are resident at once (8 per CU in FP32, 5 in
+    // FP64), two have fewer to run after that, until they need another round
+    // themselves (8 per CU in FP32, 5 or, D3Q27, 4 in FP64): then four are ahead
+    // again, in FP32 where that round is less than a third full and few went
+    // before. us with 2 and 4: FP32 D3Q27 61 k groups 15.0 and 12.2, 127 k 17.7 and
+    // 15.1, 152 k 19.1 and 21.2, 219 k 23.1 and 24.9, 292 k 34.9 and 31.6, 520 k 53.6 and
+    // 56.0; FP64 D3Q27 65 k 17.6 and 16.4, 97 k 26.4 and 29.9, 152 k 39.5 and 38.1. With
+    // the discontinuous coupling each of them looks up the faces: 33 k groups 9.6 and
+    // 9.1, 152 k 17.4 and 19.5.
     static int assembly_split(int64_t n, bool dg)
     {
         constexpr int64_t cu = 256;
-        if (dg) return n <= 160 * cu ? 4 : 2;
-        if (!kSplit2) return 4;
+        if (dg) return n <= 144 * cu ? 4 : 2;
         constexpr int64_t r4 = 64 * cu * (sizeof(T) == 4 ? 8 : 5);
-        constexpr int64_t r2 = sizeof(T) == 8 ? 2 * r4 : 128 * cu * (Q == 27 ? 7 : 8);
-        return n <= r4 || (n > r2 && (sizeof(T) == 8 || 40 * (n % r2) < 13 * r2)) ? 4 : 2;
+        constexpr int64_t r2 = 128 * cu * (sizeof(T) == 4 ? 8 : Q == 27 ? 4 : 5);
+        if (n <= r4) return 4;
+        if (sizeof(T) == 8) return n > r2 ? 4 : 2;
+        return Q != 9 && n > r2 && n < 3 * r2 && 3 * (n % r2) < r2 ? 4 : 2;
     }
 
     static int launch_group(sel_sim *s, const GroupArgs<T> &B)
@@ -323,15 +324,20 @@ struct Impl {
         // the discontinuous coupling adds its interface flux here
         const int split = assembly_split(s->ngrp, B.nbr != nullptr);
         const dim3 grid((unsigned)xcd_grid((s->ngrp * split + 255) / 256));
-        if (B.nbr && split == 4) {
-            hipLaunchKernelGGL((k_group_split<Q, T, 4, N>), grid, block, 0, s->stream, B);
-        } else if (B.nbr) {
-            hipLaunchKernelGGL((k_group_split<Q, T, 2, N>), grid, block, 0, s->stream, B);
-        } else if (split == 4) {
-            hipLaunchKernelGGL((k_group_split<Q, T, 4>), grid, block, 0, s->stream, B);
-        } else if constexpr (kSplit2) {
-            hipLaunchKernelGGL((k_group_split<Q, T, 2>), grid, block, 0, s->stream, B);
-        }
+        auto launch = [&](auto FN) {
+            constexpr bool fn = decltype(FN)::value;
+            if (B.nbr && split == 4) {
+                hipLaunchKernelGGL((k_group_split<Q, T, 4, N, fn>), grid, block, 0, s->stream, B);
+            } else if (B.nbr) {
+                hipLaunchKernelGGL((k_group_split<Q, T, 2, N, fn>), grid, block, 0, s->stream, B);
+            } else if (split == 4) {
+                hipLaunchKernelGGL((k_group_split<Q, T, 4, 0, fn>), grid, block, 0, s->stream, B);
+            } else {
+                hipLaunchKernelGGL((k_group_split<Q, T, 2, 0, fn>), grid, block, 0, s->stream, B);
+            }
+        };
+        if (B.Fn) launch(std::true_type{});
+        else launch(std::false_type{});
         SEL_LAUNCH_CHECK();
         return toc(s, ev);
     }
