@@ -113,7 +113,7 @@ Plan make_plan(const sel_mesh *m, const sel_params *p)
     L.tabF = carve(c, ts * n1 * n1);
     L.tabW = carve(c, ts * n1);
     if (m->dim == 3) L.tabL = carve(c, ts * sel::kLineTab);
-    if (!m->aff.empty()) L.aff = carve(c, ts * m->aff.size());
+    if (!m->aff.empty() && sel::affine_pass(m->N, p->Q, p->precision, E * np, m->dg)) L.aff = carve(c, ts * m->aff.size());
     L.geoD = carve(c, 8 * n1 * n1);
     L.geoW = carve(c, 8 * n1);
     L.pcode = carve(c, 4 * np);
@@ -376,7 +376,7 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     s->tabF = b + L.tabF;
     s->tabW = b + L.tabW;
     if (m->dim == 3) s->tabL = b + L.tabL;
-    if (!m->aff.empty()) s->aff = b + L.aff;
+    if (L.aff) s->aff = b + L.aff;
     s->geoD = reinterpret_cast<double *>(b + L.geoD);
     s->geoW = reinterpret_cast<double *>(b + L.geoW);
     s->pcode = reinterpret_cast<int32_t *>(b + L.pcode);

@@ -14,6 +14,25 @@ namespace sel {
 constexpr int kMaxN1 = 16;  // host tables up to N = 15
 constexpr int kMaxQ = 27;
 constexpr int kOwn = 1 << 30;  // node table: the node's first copy (kernels_flat.h)
+// Meshes of affine elements that take the streaming pass made for them
+// (kernels_stream.h); the others take the general kernels for curved elements.
+// A low-order element gives the pass few lines, and where many of them fill the
+// chip anyway the general kernels move fewer bytes per wavefront. us per step,
+// pass and general: N = 3 D3Q27 FP64 10^3 80 and 86, 12^3 118 and 104, 16^3 238 and
+// 200, 28^3 1362 and 1288; FP32 12^3 87 and 87 (D3Q19 66 and 71), 16^3 146 and 122; N = 2 FP64 D3Q27 12^3
+// 75 and 81, 16^3 131 and 104; N = 4 D3Q27 FP32 8^3 58 and 84, 12^3 128 and 121, 16^3 254
+// and 227, 24^3 (a state of 187 MB) 862 and 872; FP64 10^3 121 and 113, 16^3 402 and
+// 387, 18^3 (157 MB) 598 and 624; N = 5 D3Q27 14^3 421 and 499. Discontinuous
+// coupling: N = 3 FP64 12^3 136 and 126, FP32 12^3 84 and 92, 16^3 165 and 152, N = 4
+// 16^3 519 and 533.
+inline bool affine_pass(int N, int Q, int prec, int64_t nodes, bool dg)
+{
+    const bool f64 = prec == SEL_FP64;
+    if (N <= 3) return nodes < (f64 ? 100000 : dg ? 200000 : N == 3 ? 130000 : 100000);
+    if (N > 4 || dg) return true;
+    return nodes < (f64 ? 100000 : 200000) || nodes * Q * (f64 ? 8 : 4) >= 128000000;
+}
+
 constexpr int kLineTab = 2 * (2 * (kMaxN1 / 2 + 1) * (kMaxN1 / 2));  // values of the two mirrored line tables at most
 
 // Host-side tables of the spectral element (built in tables.cpp).

@@ -1,4 +1,4 @@
-"""3D and 2D meshes on both sides of the sizes at which a kernel or its split
+"""Meshes on both sides of the sizes at which a kernel or its split
 changes, against the FP64 oracle: low orders with many shared nodes, affine and
 curved (one node moved by 1e-9 of the spacing), with and without the filter.
 
@@ -78,3 +78,16 @@ def test_first_stage_small(N, Q, filt):
                                      (6, 19, (11, 11, 10))])
 def test_first_stage_large(N, Q, nel, filt):
     check(curved(box(N, Q, nel, filt, walls=True)))
+
+
+# affine meshes of low order: streaming pass below a size, general kernels above
+# (one case each side), N = 4 the pass again for a state of 128 MB
+@pytest.mark.parametrize("N,Q,nel", [(2, 27, (14, 14, 14)), (2, 19, (16, 16, 15)), (3, 19, (11, 11, 11)), (3, 27, (12, 12, 12)),
+                                     (4, 27, (9, 9, 9)), (4, 19, (12, 12, 12)), (4, 27, (18, 17, 16))])
+def test_affine_low_orders(N, Q, nel):
+    check(box(N, Q, nel, "quad", walls=True))
+    if nel[0] < 15:
+        check(box(N, Q, nel))
+        check(box(N, Q, nel, coupling="dg"), 1)
+        c = box(N, Q, nel, "quad")
+        check(c, 1, F=np.broadcast_to([1e-3, 2e-3, -1e-3], (c.E, c.np_, 3)).copy())
