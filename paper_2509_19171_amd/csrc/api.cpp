@@ -137,7 +137,7 @@ Plan make_plan(const sel_mesh *m, const sel_params *p)
     if (m->dg) L.nbr = carve(c, 4 * m->nbr.size());
     L.hidx = carve(c, 4 * (size_t)(m->ngrp + 1));
     L.rhoc = carve(c, ts * (size_t)Gtot);
-    if (m->dim == 2 && !m->dg) {
+    if (m->dim == 2 && sel::flat_2d(m->N, p->precision, E * np, m->dg)) {
         L.nodes = carve(c, sizeof(int4) * (size_t)(E * np));
         L.rtb2 = carve(c, ts * (size_t)p->Q * (size_t)m->plane);
         L.rhoc2 = carve(c, ts * (size_t)Gtot);
@@ -406,7 +406,7 @@ extern "C" int sel_init(const sel_mesh *m, const sel_params *p, const double *rh
     s->nmp = m->nmp;
     s->rhoc = b + L.rhoc;
     s->Fn = b + L.Fn;
-    if (m->dim == 2 && !m->dg) {
+    if (L.nodes) {
         s->nodes = reinterpret_cast<int4 *>(b + L.nodes);
         s->rtb2 = b + L.rtb2;
         s->rhoc2 = b + L.rhoc2;

@@ -1,11 +1,10 @@
-// Stage kernels of 2D meshes (D2Q9, continuous coupling). 2D states are small
-// and a launch of a few microseconds costs as much as its work, so a stage is
-// one kernel: the shared-node assembly of a stage is done by the kernel of the
-// next one, which reads the contributions of a boundary node's members and
-// combines them itself (every copy the same way; the owning copy stores the
-// value where a later stage needs it). A separate assembly had doubled the
-// launches: 64 elements N = 5 FP64 took 6.3 + 4.0 us per stage, 1024 elements N =
-// 7 FP32 7.4 + 4.8.
+// Stage kernels of small 2D meshes (D2Q9; sel::flat_2d says which). A launch of
+// a few microseconds costs as much as its work there, so a stage is one kernel:
+// the shared-node assembly of a stage is done by the kernel of the next one,
+// which reads the contributions of a boundary node's members and combines them
+// itself (every copy the same way; the owning copy stores the value where a
+// later stage needs it). A separate assembly doubles the launches: 64 elements
+// N = 5 FP64 took 6.3 + 4.0 us per stage, 1024 elements N = 7 FP32 7.4 + 4.8.
 //
 // What a kernel reads of other elements' boundary nodes (the contributions of
 // the last stage and the two states it combines) no kernel writes at the same
@@ -16,7 +15,9 @@
 // One thread per node and all velocities in registers; the node table [E][NP]
 // (interior slot or group, contribution slot, members and owner, extra rank
 // index) makes every address known after one load. Blocks of about one
-// wavefront: the smallest meshes still spread over the chip.
+// wavefront: the smallest meshes still spread over the chip. With the
+// discontinuous coupling a node has one copy and nothing is pending: the assembly
+// with the interface flux stays a kernel of its own.
 #pragma once
 
 #include "kernels_impl.h"
@@ -38,7 +39,7 @@ template <typename T>
 struct FlatArgs {
     const T *op;          // operand: interior nodes, and boundary nodes when nothing is pending
     const T *f0in;        // stage: post-collision state (interior)
-    T *out;               // result: interior nodes (filter: all; may be op, with an assembly pending)
+    T *out;               // result: interior nodes (filter: all; may be op)
     T *y;                 // first stage: post-collision state
     T *opb;               // stage: the operand's boundary nodes are stored here
     // pending assembly of the operand's boundary nodes: pca f0 + pcb fk + pcc L

@@ -451,8 +451,8 @@ struct Impl {
 
     // First stage: filter (when pending) and collide the state S into the
     // post-collision state y = F0, then FA = y + cc L(y), by a streaming pass like
-    // the later stages' or in the same kernel (first_stage). (2D: the
-    // discontinuous coupling alone.)
+    // the later stages' or in the same kernel (first_stage; 2D: with the
+    // continuous coupling, whose shared nodes need no value of another element).
     static int stage_one(sel_sim *s, StageArgs<T> &A, GroupArgs<T> &B, const T *S, T *F0, T *FA, double cc,
                          bool pending)
     {
@@ -485,9 +485,19 @@ struct Impl {
             A.op = S;
             A.f0out = F0;
             A.filter = pending ? 1 : 0;
-            A.collide_only = 1;
+            A.collide_only = s->nbr != nullptr;
+            A.out = FA;
+            A.ca = T(0);
+            A.cb = T(1);
+            A.cc = T(cc);
             if (int rc = launch_stage<M_STAGE1>(s, A)) return rc;
-            return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
+            if (s->nbr) return stage_pass(s, A, B, F0, F0, FA, 0.0, 1.0, cc);
+            B.f0 = B.fk = F0;
+            B.out = FA;
+            B.ca = T(0);
+            B.cb = T(1);
+            B.cc = T(cc);
+            return launch_group(s, B);
         }
     }
 
@@ -529,14 +539,15 @@ struct Impl {
         return toc(s, ev);
     }
 
-    // 2D, continuous coupling: one kernel per stage (kernels_flat.h). Arrays: X
-    // the state, whose interior the first stage overwrites with its stage value
-    // and the last one with the result; Y the post-collision state; B = f[cur^1]
-    // the second stage value; Z the printed stages' third. A stage's boundary
-    // values are pending (in its contributions, to be combined from the two
-    // states f0 and fk) until the next kernel has assembled them, so no kernel
-    // may write the boundary part of those two: with SSPRK3, where Y is one of
-    // them, it alternates between f[2] and f[3].
+    // 2D, one kernel per stage (kernels_flat.h). Arrays: X the state, whose
+    // interior the first stage overwrites with its stage value and the last one
+    // with the result; Y the post-collision state; W = f[cur^1] the second stage
+    // value; Z the printed stages' third. A stage's boundary values are pending
+    // (in its contributions, to be combined from the two states f0 and fk) until
+    // the next kernel has assembled them, so no kernel may write the boundary
+    // part of those two: with SSPRK3, where Y is one of them, it alternates
+    // between f[2] and f[3]. With the discontinuous coupling the assembly, which
+    // looks across the faces, runs on its own before the next kernel.
     static int step_flat(sel_sim *s, int64_t nsteps)
     {
         using FG = FlatGeo<N>;
@@ -595,12 +606,12 @@ struct Impl {
             A.pcc = T(cc);
             A.pend = 1;
         };
-        auto assemble = [&]() -> int {
+        auto assemble = [&](T *out) -> int {
             B.rtb = rt[kt];
             B.rhoc = rh[kr];
             B.f0 = A.pf0;
             B.fk = A.pfk;
-            B.out = X;
+            B.out = out;
             B.ca = A.pca;
             B.cb = A.pcb;
             B.cc = A.pcc;
@@ -609,6 +620,8 @@ struct Impl {
         };
         // out = ca f0 + cb fk + cc L(fk), fk pending from before
         auto stage = [&](T *fk, const T *f0, T *out, double ca, double cb, double cc) -> int {
+            if (s->nbr)
+                if (int rc = assemble(fk)) return rc;
             A.op = A.opb = fk;
             A.f0in = f0;
             A.out = out;
@@ -622,10 +635,10 @@ struct Impl {
         A.filter = 0;
         for (int64_t n = 0; n < nsteps; ++n) {
             A.dtau = nullptr;
+            // the features read the state: it is assembled first
+            if (A.pend && (s->nbr || s->closure_on))
+                if (int rc = assemble(X)) return rc;
             if (s->closure_on) {
-                // the features read the state: it is assembled first
-                if (A.pend)
-                    if (int rc = assemble()) return rc;
                 if (int rc = closure_increments(s, A.filter != 0)) return rc;
                 A.dtau = s->cl_dtau;
             }
@@ -651,11 +664,14 @@ struct Impl {
             s->time += dt;
             s->nstep += 1;
         }
-        if (!filt) return assemble();
+        if (!filt || s->nbr)
+            if (int rc = assemble(X)) return rc;
+        if (!filt) return SEL_OK;
         // in place: a node's interior value is read by its own thread alone, and its
         // boundary value comes from the two states it is pending on, neither of
-        // them X. The state keeps its array from call to call, so a captured call
-        // (or a sequence of them) replays from its own result.
+        // them X (discontinuous coupling: is the thread's own as well). The state
+        // keeps its array from call to call, so a captured call (or a sequence of
+        // them) replays from its own result.
         A.op = A.out = X;
         return launch(std::integral_constant<int, F_FILTER>{}, 3);
     }
@@ -664,7 +680,7 @@ struct Impl {
     {
         if (nsteps <= 0) return SEL_OK;
         if constexpr (DIM == 2) {
-            if (!s->nbr) return step_flat(s, nsteps);
+            if (s->nodes) return step_flat(s, nsteps);
         }
         const double dt = s->p.dt;
         const bool filt = s->p.filter_type != SEL_FILTER_NONE;

@@ -14,6 +14,26 @@ namespace sel {
 constexpr int kMaxN1 = 16;  // host tables up to N = 15
 constexpr int kMaxQ = 27;
 constexpr int kOwn = 1 << 30;  // node table: the node's first copy (kernels_flat.h)
+// 2D meshes that take one kernel per stage (kernels_flat.h); larger ones take the
+// general kernels with an assembly of their own. The one kernel saves launches
+// and the assembly's trip through memory as long as the mesh is small; past
+// that its gathers (every copy of a shared node reads the contributions of all)
+// and, at orders whose element leaves lanes of a wavefront idle (N = 5: 36 of 64,
+// N = 8: 81 of 128), its smaller workgroups cost more. Largest element-node counts
+// in thousands, N = 2 .. 10; us per step, one kernel and general: FP64 N = 4 140 k 48
+// and 50, 275 k 83 and 75, N = 5 58 k 33 and 38, 130 k 59 and 49, 1.0 M 372 and 201; N = 7
+// 231 k 65 and 65, 937 k 211 and 190; N = 10 213 k 69 and 74, 874 k 212 and 199; FP32 N = 4
+// 140 k 35 and 42, 275 k 59 and 55; N = 7 937 k 115 and 121, 1.9 M 255 and 216. With the
+// discontinuous coupling, where the nodes are assembled apart in either case, the
+// one kernel stays ahead longer, unless its lanes are idle: FP64 N = 7 462 k 130 and
+// 143, 1.9 M 548 and 545, N = 5 129 k 63 and 60.
+inline bool flat_2d(int N, int prec, int64_t nodes, bool dg)
+{
+    constexpr int most[2][9] = {{900, 700, 200, 90, 180, 350, 80, 250, 300}, {140, 230, 200, 190, 360, 1200, 160, 1200, 1200}};
+    const int64_t m = 1000 * (int64_t)most[prec == SEL_FP64 ? 0 : 1][N - 2];
+    return nodes <= (dg && N != 5 && N != 8 ? 4 * m : m);
+}
+
 // Meshes of affine elements that take the streaming pass made for them
 // (kernels_stream.h); the others take the general kernels for curved elements.
 // A low-order element gives the pass few lines, and where many of them fill the
@@ -144,7 +164,7 @@ struct sel_sim {
     void *f[4] = {};           // T [nstate]: state, f0, stage a, stage b
     void *rtb = nullptr;       // T [Q][plane] element contributions of boundary nodes
     void *rhoc = nullptr;      // T [Gtot]
-    // 2D, continuous coupling (kernels_flat.h): node table and second buffers
+    // 2D meshes that take the kernels of kernels_flat.h: node table and second buffers
     int4 *nodes = nullptr;     // [E][np]
     void *rtb2 = nullptr, *rhoc2 = nullptr;
     double *io = nullptr;      // FP64 [E][np][dim+1] (moments / per-velocity transfers)

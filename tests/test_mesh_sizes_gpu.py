@@ -91,3 +91,87 @@ def test_affine_low_orders(N, Q, nel):
         check(box(N, Q, nel, coupling="dg"), 1)
         c = box(N, Q, nel, "quad")
         check(c, 1, F=np.broadcast_to([1e-3, 2e-3, -1e-3], (c.E, c.np_, 3)).copy())
+
+
+# 2D: one kernel per stage below a size, general kernels above. The step is
+# compared with the same step put together from the operators of sel_apply, which
+# run the general kernels on the same metric (against the oracle the rounding of
+# the coordinates, which grows with the number of elements, would be what shows).
+# Bound: a stage adds dt L, sums of at most N + 1 <= 11 products of the order of
+# the populations (0.44 in FP64, the deviations of 0.01 in FP32) with dt c D_iq of
+# order 1 at this time step, so 11 x 0.44 x 1.1e-16 x a few per stage, four passes:
+# 1e-13; FP32 11 x 0.01 x 6e-8 x a few: 1e-7.
+def channel(N, nel, filt=None, coupling="cg"):
+    c = I.case_poiseuille(nelx=nel[0], nely=nel[1], N=N, curved=True, filt=filt)
+    c.rho, c.u = I.random_state(c, seed=N, amp=0.01)
+    c.g = (1e-3, -2e-3, 0.0)
+    c.coupling = coupling
+    return c
+
+
+def step_from_operators(sim, c):
+    """f after one SSPRK3 step (Secs. 2.1, 2.2, 2.2.3), [E][Q][np]."""
+    import oracle
+
+    e, t, _ = oracle.lattice(c.dim, c.Q)
+    e = np.asarray(e, dtype=float)[:, :c.dim]
+    y = sim.apply("collide", sim.get_f())
+    rho = y.sum(1, keepdims=True)
+    Fs = (3.0 * np.asarray(t) * (e @ np.asarray(c.g)[:c.dim]))[None, :, None] * rho
+
+    def L(f):
+        return sim.apply("rhs", f) + Fs
+
+    w = y + c.dt * L(y)
+    w = 0.75 * y + 0.25 * (w + c.dt * L(w))
+    f = y / 3.0 + 2.0 / 3.0 * (w + c.dt * L(w))
+    return sim.apply("filter", f) if c.filter else f
+
+
+def check_operators(c):
+    from paper_2509_19171_amd import sel
+
+    for prec, tol in (("fp64", 1e-13), ("fp32dev", 1e-7)):
+        sim = sel.from_case(c, prec)
+        ref = step_from_operators(sim, c)
+        f0, rho = sim.get_f(), sim.moments()[0]
+        sim.step(1)
+        err = np.abs(sim.get_f() - ref).max()
+        print(f"[gpu] {c.name} N {c.N} E {c.E} {c.coupling} {c.filter} {prec}: f {err:.2e}", flush=True)
+        assert err < tol
+        # the body force given as a force per node: the same step
+        d = dataclasses.replace(c, g=(0.0, 0.0, 0.0))
+        sim = sel.from_case(d, prec)
+        sim.set_f(f0)
+        sim.set_force(rho[..., None] * np.asarray(c.g)[:c.dim])
+        sim.step(1)
+        err = np.abs(sim.get_f() - ref).max()
+        print(f"[gpu]   force per node: f {err:.2e}", flush=True)
+        assert err < tol
+
+
+@pytest.mark.parametrize("coupling", ["cg", "dg"])
+def test_2d_sizes(coupling):
+    check_operators(channel(8, (45, 44), "quad", coupling))
+
+
+@pytest.mark.parametrize("N,nel", [(2, (130, 125)), (4, (92, 90)), (5, (75, 72))])
+def test_2d_sizes_oracle(N, nel):
+    c = channel(N, nel, "quad" if N > 2 else None)
+    check(c)
+    check(dataclasses.replace(c, rk="printed4", filter=None), 1,
+          F=np.broadcast_to([1e-3, -2e-3], (c.E, c.np_, 2)).copy())
+
+
+@pytest.mark.parametrize("coupling", ["cg", "dg"])
+@pytest.mark.parametrize("filt", [None, "quad"])
+@pytest.mark.parametrize("N", [3, 5, 8, 10])
+def test_2d_small(N, filt, coupling):
+    check_operators(channel(N, (5, 4), filt, coupling))
+
+
+@pytest.mark.parametrize("filt", [None, "quad"])
+@pytest.mark.parametrize("rk", ["ssprk3", "printed4"])
+@pytest.mark.parametrize("N", [3, 5, 8])
+def test_2d_discontinuous_stages(N, rk, filt):
+    check(dataclasses.replace(channel(N, (5, 4), filt, "dg"), rk=rk), 7)
