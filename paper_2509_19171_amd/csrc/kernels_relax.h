@@ -300,23 +300,26 @@ __global__ void __launch_bounds__((FilterGeo<N, Q, T>::BLOCK)) k_filter(RelaxArg
 // The populations are read in slot order, as runs, and the results go through
 // LDS to be written as runs in node order (one thread per node in node order
 // read six slots to a run and wrote 24-byte pieces: 16^3 elements N = 7 FP32 78
-// us, here 59; D3Q19 N = 8 89 and 69; 12^3 N = 7 FP64 41 and 33.5).
+// us, here 59; D3Q19 N = 8 89 and 69; 12^3 N = 7 FP64 41 and 33.5). Elements of more
+// than 1024 nodes take 1024 threads (N = 12 6^3 FP64: 17.9 us with 256, here 14.1).
 template <int N>
 struct MomentGeo {
     static constexpr int NP = (N + 1) * (N + 1) * (N + 1), EPB = NP >= 256 ? 1 : 256 / NP;
+    static constexpr int BLOCK = NP > 1024 ? 1024 : 256;
 };
 template <int N, int Q, typename T, bool DEV>
-__global__ void __launch_bounds__(256) k_moments_el(const T *f, const int32_t *bpos, const int32_t *bmap, int64_t E,
+__global__ void __launch_bounds__(MomentGeo<N>::BLOCK) k_moments_el(const T *f, const int32_t *bpos, const int32_t *bmap, int64_t E,
                                                     int64_t QGi, double rho0, double *rho, double *u)
 {
     using SG = StreamGeo<N, Q, T>;
-    constexpr int n1 = SG::n1, NP = SG::NP, NI = SG::NI, NB = SG::NB, M1 = N - 1, EPB = MomentGeo<N>::EPB;
+    constexpr int n1 = SG::n1, NP = SG::NP, NI = SG::NI, NB = SG::NB, M1 = N - 1, EPB = MomentGeo<N>::EPB,
+                  BLOCK = MomentGeo<N>::BLOCK;
     __shared__ double sm[4][EPB * NP];
     const int64_t nblk = (E + EPB - 1) / EPB, eb = xcd_block(nblk);
     if (eb >= nblk) return;  // whole workgroup
     const int64_t left = E - eb * EPB;
     const uint32_t nodes = (left < EPB ? (int)left : EPB) * NP;
-    for (uint32_t q = threadIdx.x; q < nodes; q += 256) {
+    for (uint32_t q = threadIdx.x; q < nodes; q += BLOCK) {
         const uint32_t le = q / NP, s = q % NP;
         const int64_t e = eb * EPB + le;
         uint32_t p, st;
@@ -347,8 +350,8 @@ __global__ void __launch_bounds__(256) k_moments_el(const T *f, const int32_t *b
     }
     __syncthreads();
     const int64_t o = eb * EPB * NP;
-    for (uint32_t q = threadIdx.x; q < nodes; q += 256) rho[o + q] = sm[0][q];
-    for (uint32_t q = threadIdx.x; q < 3 * nodes; q += 256) u[3 * o + q] = (&sm[1][0])[q];
+    for (uint32_t q = threadIdx.x; q < nodes; q += BLOCK) rho[o + q] = sm[0][q];
+    for (uint32_t q = threadIdx.x; q < 3 * nodes; q += BLOCK) u[3 * o + q] = (&sm[1][0])[q];
 }
 
 // The collision alone, one thread per node id. op and out may be the same.

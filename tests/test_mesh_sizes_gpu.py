@@ -93,6 +93,23 @@ def test_affine_low_orders(N, Q, nel):
         check(c, 1, F=np.broadcast_to([1e-3, 2e-3, -1e-3], (c.E, c.np_, 3)).copy())
 
 
+# density and velocity are sums of the same populations (FP64; |f| < 0.5, 19 terms)
+@pytest.mark.parametrize("N,Q,nel", [(12, 19, (2, 2, 2)), (12, 19, (5, 4, 4)), (7, 27, (3, 2, 2)), (2, 27, (5, 5, 4))])
+def test_moments_of_the_state(N, Q, nel):
+    import oracle
+    from paper_2509_19171_amd import sel
+
+    c = box(N, Q, nel, walls=True)
+    e = np.asarray(oracle.lattice(3, Q)[0], dtype=float)
+    for prec in ("fp64", "fp32dev"):
+        sim = sel.from_case(c, prec)
+        sim.step(1)
+        f = sim.get_f()
+        rho, u = sim.moments()
+        r = f.sum(1)
+        assert np.abs(rho - r).max() < 1e-14 and np.abs(u - np.einsum("eqp,qk->epk", f, e) / r[..., None]).max() < 1e-14
+
+
 # 2D: one kernel per stage below a size, general kernels above. The step is
 # compared with the same step put together from the operators of sel_apply, which
 # run the general kernels on the same metric (against the oracle the rounding of
