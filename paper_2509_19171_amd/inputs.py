@@ -19,7 +19,7 @@ velocity is ``wall_u[k-1]``. Lattice units: speed 1, c_s^2 = 1/3.
 from __future__ import annotations
 
 import math
-from dataclasses import dataclass, field
+from dataclasses import dataclass, field, replace
 from typing import Callable, Optional
 
 import numpy as np
@@ -344,6 +344,16 @@ def case_tgv3d(nel=16, N=7, Q=27, Re=1600.0, Ma=0.1, steps=5000, filt="quad", cf
     rho, u = tgv3d_fields(mesh.xyz, u0)
     return Case("tgv3d", mesh, Q, 1.0, nu, dt, rho, u, steps, meta=dict(u0=u0, Re=Re),
                 **_filter_kw(filt, N))
+
+
+def off_affine(case: Case) -> Case:
+    """The case with one interior node moved by 1e-9 of the smallest node
+    spacing: not every element is the affine image of the reference element any
+    more, so the mesh takes the general per-node metric."""
+    n1 = case.N + 1
+    xyz = case.mesh.xyz.copy()
+    xyz[0, 1 + n1 + (n1 * n1 if case.dim == 3 else 0), 0] += 1e-9 * min_node_spacing(case.mesh)
+    return replace(case, mesh=replace(case.mesh, xyz=xyz))
 
 
 def random_state(case: Case, seed: int = 7, amp: float = 0.01):
