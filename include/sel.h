@@ -157,6 +157,10 @@ int sel_init(const sel_mesh *mesh, const sel_params *p, const double *rho, const
  * chosen Runge-Kutta form (Sec. 2.2, 2.2.1, 2.2.2), then the modal filter
  * (Sec. 2.2.3; applied lazily: ahead of the next step's collision, or
  * run at the end of the call, so the state seen after the call is filtered).
+ * The call issues kernel launches only and can be captured in a graph. A graph
+ * of calls advances the state at every replay if they leave it in the array
+ * they found it in: calls without a filter do, and so does an even number of
+ * calls with one.
  * Errors: SEL_EINVAL (null sim or nsteps < 0), SEL_EDEVICE (launch failure);
  * device faults and non-finite states surface at the next synchronising call. */
 int sel_step(sel_sim *sim, int64_t nsteps);
@@ -233,7 +237,8 @@ int sel_radial_profile(sel_sim *sim, const double *origin, const double *axis, d
 int sel_get_time(const sel_sim *sim, double *t, int64_t *nstep);
 
 /* Operator pieces on a host state f [E][Q][np] (FP64 in and out), for
- * checking the kernels one by one. Synchronises.
+ * checking the kernels one by one. Synchronises. (Small 2D meshes step with
+ * kernels that take a whole stage; the pieces run the general kernels.)
  *   SEL_OP_RHS:       M^-1 (R(n.j) - C_a f) after assembly (Sec. 2.2, 2.2.1), no F*
  *   SEL_OP_RHS_LOCAL: element contributions R(n.j) - C_a f before assembly
  *   SEL_OP_COLLIDE:   post-collision f* (Sec. 2.1)
@@ -319,10 +324,11 @@ int64_t sel_mlp_work_floats(int64_t n);
 /* Loss L = mean_i (softplus(z_i) - y_i)^2 over n rows (targets y = dtau/tau)
  * and its gradient with respect to the trainable range, d_grad [8833].
  * Row i is row d_idx[i] of d_X [.][6] and d_y (d_idx: device int32 [n], or
- * NULL for rows 0..n-1; the caller keeps indices in range). The gradient
- * is summed over fixed chunks of consecutive rows (their size depends on n
- * only), then over the chunks in order, with no atomics: the same inputs give
- * the same result bit for bit. loss (host, may be NULL) synchronises. */
+ * NULL for rows 0..n-1; the caller keeps indices in range). Tiles of 16 rows
+ * are dealt to a number of workgroups that depends on n only (tile k to
+ * workgroup k modulo their number); the workgroups' sums are added in eight runs
+ * of consecutive workgroups, then run by run, with no atomics: the same inputs
+ * give the same result bit for bit. loss (host, may be NULL) synchronises. */
 int sel_mlp_gradient(const float *d_params, const float *d_X, const float *d_y, const int32_t *d_idx, int64_t n,
                      float *d_work, float *d_grad, double *loss, void *stream);
 
@@ -337,7 +343,7 @@ int sel_mlp_train_step(float *d_params, float *d_m, float *d_v, const float *d_X
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * Adam step as sel_mlp_train_step, computed by the same kernels and with the
  * same result bit for bit, but its training work memory is a fixed device
- * array inside the library (8.75 MB per GPU, held until the process ends)
+ * array inside the library (9.08 MB per GPU, held until the process ends)
  * instead of a d_work argument. It allocates nothing. n is limited to 4096
  * rows (one minibatch of the training recipe); larger n returns SEL_EINVAL.
  * Every call on a GPU uses that GPU's one array: calls that overlap on one

@@ -767,7 +767,6 @@ __global__ void __launch_bounds__((Geo<DIM, N>::BLOCK), (((MODE == M_STAGE23 || 
                 fq[a] = pl[a][p];
             });
         } else {
-            // the filter passes of the first stage used the same LDS
             static_for<0, Q>([&](auto AA) {
                 constexpr int a = decltype(AA)::value;
                 pl[a][p] = fq[a];

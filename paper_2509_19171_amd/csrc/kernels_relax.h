@@ -1,5 +1,6 @@
 // Modal filter and collision of 3D meshes (Secs. 2.2.3 and 2.1), ahead of the
-// streaming of the first Runge-Kutta stage.
+// streaming of the first Runge-Kutta stage. (Curved meshes for which
+// Impl::first_stage holds take the filter alone from here, or neither.)
 //
 // k_relax: one workgroup holds all Q planes of an element (several small
 // elements) in LDS. A thread loads its slots for every velocity, the filter
@@ -11,9 +12,9 @@
 // k_filter + k_collide: the same in two passes over the state where the planes
 // don't fit (FP64 from N = 7, N = 12): lines of one velocity per unit, then one
 // thread per node id. k_collide alone serves a step without a pending filter.
-// Measured against the fused first stage (filter, collision and streaming in
-// one kernel, up to 76 KB of LDS and 500 B of spills), as relaxation +
-// streaming pass: D3Q27 N = 7, 16^3 FP32 307 -> 98 + 125 us (3.9 TB/s); 12^3 FP64
+// Measured on affine meshes against filter, collision and streaming in one
+// kernel (up to 76 KB of LDS and 500 B of spills), as relaxation + streaming
+// pass: D3Q27 N = 7, 16^3 FP32 307 -> 98 + 125 us (3.9 TB/s); 12^3 FP64
 // 276 -> 62 + 42 + 100 (5.1 and 6 TB/s; k_relax with one workgroup per CU 103);
 // D3Q19 N = 8, 16^3 FP32 474 -> 102 + 145 (in two passes 151 + 57); N = 12, 8^3
 // FP64 889 -> 95 + 47 + 110. The filter at the end of a call: 152 -> 81, 142 -> 62,

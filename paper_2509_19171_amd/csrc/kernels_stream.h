@@ -9,7 +9,7 @@
 // grad f itself; a contribution is scaled by wJ = w_i w_j w_k J where it is
 // written. (Curved elements take k_stage23_mf, k_stage or k_stage_big: with the
 // metric per node this split was slower there, 78 against 61 us on 1024
-// elements of order 7.)
+// elements of order 7. So do larger meshes of orders 2 to 4: affine_pass.)
 //
 // The unit of work is a pair of opposite velocities of one element (they share
 // c up to its sign), with one thread per line of (N+1) nodes.
@@ -25,11 +25,12 @@
 // node and velocity that is 10 LDS accesses and 3 (N+1)/2 + O(1) multiply-adds
 // (LineTab), against 26 and 3 (N+1) with one thread per node.
 //
-// Measured per launch against the general kernels (MI355X, memory-bound at
-// about 4 TB/s of L2 misses: operand with the copies of shared nodes, f0, update
-// and contributions): D3Q27 N = 7, 16^3 elements FP32 180 -> 136 us, 12^3 FP64
-// 164 -> 114; D3Q19 N = 8, 16^3 FP32 304 -> 161; N = 12, 8^3 FP64 539 -> 121;
-// N = 5, 10^3 FP32 24 -> 19; N = 3, 8^3 FP32 14 -> 8.
+// Memory-bound: D3Q27 N = 7, 16^3 elements FP32 reads 280 MB and writes 263 MB by
+// the counters (operand, f0, update, contributions) in 131 us, 4.1 TB/s, where a
+// large copy reaches 4.9; L2 misses are 592 MB, and wavefronts wait 53% of their
+// cycles. 12^3 FP64: 422 MB in 117 us. Per launch against the general kernels:
+// D3Q27 N = 7 16^3 FP32 180 -> 131 us, 12^3 FP64 164 -> 117; D3Q19 N = 8 16^3 FP32 304 ->
+// 161; N = 12 8^3 FP64 539 -> 121; N = 5 10^3 FP32 24 -> 19; N = 3 8^3 FP32 14 -> 8.
 //
 // A unit never waits for another one: with (N+1)^2 <= 64 lines it lives inside
 // one wavefront and no workgroup barrier is left, so the loads of some units
