@@ -228,3 +228,34 @@ def test_2d_small(N, filt, coupling):
 @pytest.mark.parametrize("N", [3, 5, 8])
 def test_2d_discontinuous_stages(N, rk, filt):
     check(dataclasses.replace(channel(N, (5, 4), filt, "dg"), rk=rk), 7)
+
+
+# the closure's increments reach the collision on every path: curved 3D (joined first
+# stage), 2D one kernel per stage and general, both couplings. Bounds as for the other
+# closure runs (FP32 features and weights on both sides): 1e-8 and 1e-5.
+@pytest.mark.parametrize("make", [lambda: I.off_affine(box(3, 27, (3, 2, 2), "quad")), lambda: I.off_affine(box(4, 19, (3, 2, 2))),
+                                  lambda: I.off_affine(box(5, 27, (2, 2, 2), "quad", walls=True)),
+                                  lambda: I.off_affine(box(7, 19, (2, 1, 2), "quad")), lambda: channel(5, (6, 5), "quad"),
+                                  lambda: channel(5, (6, 5), None, "dg"), lambda: channel(8, (45, 44), "quad"),
+                                  lambda: channel(8, (45, 44), "quad", "dg")])
+def test_closure_on_every_path(make):
+    import oracle
+    from oracle import closure as C
+    from paper_2509_19171_amd import sel
+
+    c = make()
+    o = oracle.from_case(c)
+    X = C.features(o).reshape(-1, 6)
+    blob = I.closure_blob(7, mean=X.mean(0), std=np.abs(X).max(0) + 1e-30, b4=0.5)
+    C.step_with_closure(o, C.unpack(blob.astype(np.float64)), 2)
+    rho_o, u_o = o.moments()
+    for prec, tol in (("fp64", 1e-8), ("fp32dev", 1e-5)):
+        g = sel.from_case(c, prec, closure=blob)
+        g.step(2)
+        rho, u = g.moments()
+        plain = sel.from_case(c, prec)
+        plain.step(2)
+        acts = uerr(plain.moments()[1], u_o)
+        print(f"[gpu] {c.name} N {c.N} E {c.E} {prec}: rho {nerr(rho, rho_o):.2e} u {uerr(u, u_o):.2e} acts {acts:.2e}", flush=True)
+        assert nerr(rho, rho_o) < tol and uerr(u, u_o) < tol, prec
+        assert acts > 10 * uerr(u, u_o)
